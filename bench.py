@@ -108,9 +108,26 @@ def tuned_matches(rec):
     return same_dev and rec.get("solver_source_sha256_16") == solver_sha()
 
 
+# On these levels the library's own launch choice is the register-resident
+# solver, several times faster than any shape of the general one; the
+# committed shapes of those levels apply only when a file is given by hand.
+RESIDENT_LEVELS = range(3, 7)
+
+
+def runs_resident(ctx, l):
+    grid, block, nu, lds = ctx.get_launch(l)
+    return l in RESIDENT_LEVELS and grid == 0 and lds == 0 and (nu == 0 or (block == 0 and nu == 1))
+
+
+def resident_bytes(l, nobs, particles):
+    """what a resident solve moves: the coefficients in, the responses out"""
+    return particles * (8.0 * (2 << (2 * l)) + 8.0 * nobs)
+
+
 def load_tuned(path, ctxs):
-    """apply committed launch shapes {form: {level: shape}} when they were
-    tuned on this device for this solver source; returns the path or None"""
+    """apply committed launch shapes {form: {level: shape}} of the general
+    solver's levels when they were tuned on this device for this solver
+    source; returns the path or None"""
     try:
         rec = json.load(open(path))
     except (OSError, ValueError):
@@ -119,6 +136,8 @@ def load_tuned(path, ctxs):
         return None
     for form, c in ctxs.items():
         for lv, sh in rec.get(form, {}).items():
+            if int(lv) in RESIDENT_LEVELS:
+                continue
             c.set_launch(int(lv), sh["grid"], sh["block"], sh.get("nu", 0), sh.get("lds", 0))
     return path
 
@@ -1093,8 +1112,10 @@ def main():
         shapes_m = {int(k): v for k, v in rec.get("mixed", {}).items()}
         for c, sh_ in ((ctx, shapes), (ctxm, shapes_m)):
             for lv, sh in sh_.items():
+                if lv in RESIDENT_LEVELS and not args.tuned:
+                    continue
                 c.set_launch(lv, sh["grid"], sh["block"], sh.get("nu", 0), sh.get("lds", 0))
-        extras["solver_launch"] = {f"h=1/{1 << lv}": sh for lv, sh in shapes.items()}
+        extras["solver_launch"] = {f"h=1/{1 << lv}": list(ctx.get_launch(lv)) for lv in shapes}
         extras["solver_launch_source"] = os.path.relpath(tuned_file, ROOT)
         log(f"solver launch shapes from {tuned_file}")
     elif not args.no_autotune:
@@ -1185,7 +1206,8 @@ def main():
     solves = args.steps * W["n_mcmc"] * J
     value = solves / dt
     nu_l = ctx.get_launch(l)[2]
-    alg = solve_bytes(l, nobs, ps["items"], ps["iters"], b_iter(nu_l))
+    res = runs_resident(ctx, l)
+    alg = resident_bytes(l, nobs, ps["items"]) if res else solve_bytes(l, nobs, ps["items"], ps["iters"], b_iter(nu_l))
     avg_ms = ps["ms"] / max(1, ps["launches"])
     achieved = alg / ps["launches"] / (avg_ms * 1e-3) / 1e9 if ps["launches"] else 0.0
     gemm_flops = 2.0 * pg["items"] * K * (2 << (2 * l))
@@ -1215,7 +1237,7 @@ def main():
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE x2.0 + WRITE_SIZE x1.0)",
                      "algorithmic_bytes_per_launch": round(alg / max(1, ps["launches"]), 0),
-                     "kernel": "solve_kernel (h=1/64, FP64)", "launch_shape": list(ctx.get_launch(l))},
+                     "kernel": f"{'resident' if res else 'solve'}_kernel (h=1/64, FP64)", "launch_shape": list(ctx.get_launch(l))},
         "cpu_baseline": cpu,
         **extras,
     }

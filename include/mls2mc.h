@@ -528,7 +528,11 @@ int mls2mc_autotune(mls2mc_ctx* ctx, int l, int64_t N, double* best_ms, void* st
  * lds_bytes 0 = built-in default; lds_bytes -1 = no LDS residency, else
  * the per-workgroup LDS budget in bytes, at most the device's LDS per
  * workgroup less 1 KiB; 160 KiB on gfx950), e.g. to restore tuned
- * schedules cached by the caller.                                          */
+ * schedules cached by the caller.  With everything default (nu 1 counts as
+ * default), or everything but the block and that one the level's default
+ * block, levels h = 1/8 .. 1/64 run the register-resident solver, which has
+ * launch shapes of its own; the autotuner tries it first and returns it as
+ * {0, default block, 0, 0}.                                                */
 int mls2mc_get_launch(const mls2mc_ctx* ctx, int l, int* grid, int* block, int* nu, int* lds_bytes);
 int mls2mc_set_launch(mls2mc_ctx* ctx, int l, int grid, int block, int nu, int lds_bytes);
 

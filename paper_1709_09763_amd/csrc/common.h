@@ -203,12 +203,17 @@ struct FwdItem {
     int32_t* iters;
 };
 int forward_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items, hipStream_t s);
-struct ListChunk {  // one prepared (grouped GEMM, work-list solve) pair
+struct ListLevel {  // the items of one level that the resident solver takes
+    int l, first, n;
+    int64_t total;
+};
+struct ListChunk {  // one prepared grouped GEMM and the solves of its items
     const GemmItem* gemm;
-    const SolveItem* solve;
-    int n;
-    int64_t tiles, total;
+    const SolveItem* solve;  // the first n_list of n: the work-list kernel's
+    int n, n_list;
+    int64_t tiles, total;    // total: particles of the work-list kernel's items
     int lmax;
+    std::vector<ListLevel> levels;
 };
 int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items, std::vector<ListChunk>& out, hipStream_t s);
 int enqueue_list(mls2mc_ctx* ctx, const std::vector<ListChunk>& chunks, hipStream_t s);

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "resident.h"
 
 namespace mls {
 
@@ -1648,6 +1649,7 @@ static bool launch_walks(int l, int bs, int nu)
 int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
 {
     if (a.N == 0) return MLS2MC_OK;
+    if (resident_level(ctx, a.l)) return launch_resident(ctx, a, s);
     if (ctx->prob.bc == MLS2MC_BC_FLOW_CELL) return launch_flow_solve(ctx, a, s);
     const int l = a.l;
     const bool mixed = a.kappa_f32;
@@ -1824,7 +1826,12 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
     for (const auto& it : items_in)
         if (it.N > 0) items.push_back(it);
     if (items.empty()) return MLS2MC_OK;
-    std::stable_sort(items.begin(), items.end(), [](const FwdItem& a, const FwdItem& b) { return a.l > b.l; });
+    // finest level first, the levels of the resident solver (a launch per
+    // level) after those of the work-list kernel
+    std::stable_sort(items.begin(), items.end(), [ctx](const FwdItem& a, const FwdItem& b) {
+        const bool ra = resident_level(ctx, a.l), rb = resident_level(ctx, b.l);
+        return ra != rb ? rb : a.l > b.l;
+    });
     const bool mixed = ctx->prob.precision == MLS2MC_MIXED;
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
     const size_t cap_bytes = 8ull << 30;
@@ -1877,6 +1884,7 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
         SolveItem* hs = (SolveItem*)(hb + off + ch.size() * sizeof(GemmItem));
         ListChunk lc;
         lc.n = (int)ch.size();
+        lc.n_list = 0;
         lc.tiles = 0;
         lc.total = 0;
         lc.lmax = 0;
@@ -1901,25 +1909,36 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
             SolveItem v;
             v.l = it.l;
             v.N = it.N;
-            v.base = lc.total;
             v.kappa = kap;
             v.G = it.G + q0 * ctx->nobs;
             v.phi = it.phi ? it.phi + q0 : nullptr;
             v.y = it.y;
             v.status = it.status ? it.status + q0 : nullptr;
             v.iters = it.iters ? it.iters + q0 : nullptr;
+            if (resident_level(ctx, it.l)) {
+                if (lc.levels.empty() || lc.levels.back().l != it.l) lc.levels.push_back({it.l, (int)i, 0, 0});
+                ListLevel& lv = lc.levels.back();
+                v.base = lv.total;
+                lv.total += it.N;
+                ++lv.n;
+            } else {
+                v.base = lc.total;
+                lc.total += it.N;
+                ++lc.n_list;
+                lc.lmax = std::max(lc.lmax, it.l);
+            }
             hs[i] = v;
-            lc.total += it.N;
-            lc.lmax = std::max(lc.lmax, it.l);
         }
         const size_t bytes = ch.size() * (sizeof(GemmItem) + sizeof(SolveItem));
         MLS_CHECK_HIP(hipMemcpyAsync(db + off, hb + off, bytes, hipMemcpyHostToDevice, s));
         lc.gemm = (const GemmItem*)(db + off);
         lc.solve = (const SolveItem*)(db + off + ch.size() * sizeof(GemmItem));
-        int64_t grid, slot;
-        int bs;
-        list_shape(ctx, lc.lmax, lc.total, mixed, &grid, &slot, &bs);
-        ws_need = std::max(ws_need, (size_t)grid * slot * esz);
+        if (lc.total > 0) {
+            int64_t grid, slot;
+            int bs;
+            list_shape(ctx, lc.lmax, lc.total, mixed, &grid, &slot, &bs);
+            ws_need = std::max(ws_need, (size_t)grid * slot * esz);
+        }
         out.push_back(lc);
         off += (bytes + 255) & ~size_t(255);
     }
@@ -1933,7 +1952,9 @@ int enqueue_list(mls2mc_ctx* ctx, const std::vector<ListChunk>& chunks, hipStrea
     const bool mixed = ctx->prob.precision == MLS2MC_MIXED;
     for (const auto& lc : chunks) {
         MLS_TRY(launch_kl_list(ctx, lc.gemm, lc.n, lc.tiles, s));
-        MLS_TRY(launch_solve_list(ctx, lc.solve, lc.n, lc.total, lc.lmax, mixed, s));
+        MLS_TRY(launch_solve_list(ctx, lc.solve, lc.n_list, lc.total, lc.lmax, mixed, s));
+        for (const ListLevel& lv : lc.levels)
+            MLS_TRY(launch_resident_list(ctx, lv.l, lc.solve + lv.first, lv.n, lv.total, mixed, s));
     }
     return MLS2MC_OK;
 }

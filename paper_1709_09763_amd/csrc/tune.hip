@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "common.h"
+#include "resident.h"
 
 namespace mls {
 
@@ -112,6 +113,14 @@ extern "C" int mls2mc_autotune(mls2mc_ctx* ctx, int l, int64_t N, double* best_m
     }
     float best = 1e30f;
     int bg = 0, bb = 0, bn = 1, bl = 0;
+    // the library's own choice first (on the small levels the resident
+    // solver, which takes no launch shape): kept when no shape beats it
+    ctx->solver_grid[l] = ctx->solver_block[l] = ctx->solver_nu[l] = ctx->solver_lds[l] = 0;
+    if (rc == MLS2MC_OK && resident_level(ctx, l)) {
+        rc = time_solve(ctx, a, s, 3, &best);
+        bb = resident_token(ctx, l);
+        bn = 0;
+    }
     for (int lds : ldsc) {
         ctx->solver_lds[l] = lds;
         for (int nu = 1; nu <= 2; ++nu) {
