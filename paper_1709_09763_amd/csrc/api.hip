@@ -3,6 +3,7 @@
 #include <new>
 
 #include "common.h"
+#include "sampler.h"
 
 namespace mls {
 
@@ -283,7 +284,7 @@ int mls2mc_create(const mls2mc_problem* p, mls2mc_ctx** out)
     int rc = build_kl_tables(ctx);
     if (rc == MLS2MC_OK) rc = build_obs_tables(ctx);
     if (rc == MLS2MC_OK) {  // the solver's work counter starts at zero and resets itself after each launch
-        if (hipMalloc(&ctx->d_queue, 2 * sizeof(unsigned long long)) != hipSuccess ||
+        if (hipMalloc(&ctx->d_queue, kStepScratchOff + kStepScratchBytes) != hipSuccess ||
             hipMemset(ctx->d_queue, 0, 2 * sizeof(unsigned long long)) != hipSuccess ||
             hipDeviceSynchronize() != hipSuccess) {
             set_error("create: device allocation failed");

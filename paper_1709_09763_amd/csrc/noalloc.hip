@@ -5,13 +5,15 @@
 #include <mutex>
 
 #include "common.h"
+#include "sampler.h"
 
 namespace mls {
 
 // prefix sums of the quantised weights of multinomial resampling (Sec. 2.4):
-// one uint64 per particle
+// one uint64 per particle, and what the many-workgroup form adds
 constexpr int64_t kNoAllocMaxN = int64_t(1) << 20;
-static __device__ __align__(256) uint64_t scratch[kNoAllocMaxN];
+constexpr int64_t kNoAllocWords = kNoAllocMaxN + 1024;
+static __device__ __align__(256) uint64_t scratch[kNoAllocWords];
 
 constexpr int kMaxDevices = 64;
 static std::mutex g_scratch_mu;
@@ -46,6 +48,7 @@ extern "C" int mls2mc_resample_noalloc(int64_t N, const double* w, const double*
     MLS_REQUIRE(N >= 1 && N <= kNoAllocMaxN,
                 "resample_noalloc: need 1 <= N <= 2^20 (the size of the library's static scratch)");
     MLS_REQUIRE(w && u && anc_out, "resample_noalloc: null pointer");
+    MLS_REQUIRE(resample_scratch(N) <= kNoAllocWords, "resample_noalloc: static scratch too small");
     uint64_t* C = nullptr;
     MLS_TRY(scratch_address(&C));
     return launch_resample_into(N, w, u, C, anc_out, (hipStream_t)stream);

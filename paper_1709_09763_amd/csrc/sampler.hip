@@ -1,121 +1,373 @@
 // Sampler kernels of MLS^2MC: the Gaussian potential (Sec. 2.1), the
 // ESS-adaptive step for tempering and bridging (Secs. 3.1, 3.2, 3.4, 4.1),
 // multinomial resampling (Sec. 2.4), and the pCN Markov move.
+#include <algorithm>
 #include <cmath>
 
 #include "common.h"
+#include "lanes.h"
+#include "sampler.h"
 
 namespace mls {
 
 // ------------------------------------------------------------ potential --
-__global__ void loglik_kernel(int64_t N, int nobs, const double* __restrict__ G,
-                              const double* __restrict__ y, double inv_sigma,
-                              double* __restrict__ phi)
+// One wave per particle: its row is read by neighbouring lanes.
+__global__ __launch_bounds__(256) void loglik_kernel(int64_t N, int nobs, const double* __restrict__ G,
+                                                     const double* __restrict__ y, double inv_sigma,
+                                                     double* __restrict__ phi)
 {
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t q = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
     if (q >= N) return;
     double s = 0.0;
-    for (int o = 0; o < nobs; ++o) {
+    for (int o = threadIdx.x & 63; o < nobs; o += 64) {
         const double r = (y[o] - G[q * nobs + o]) * inv_sigma;
         s += r * r;
     }
-    phi[q] = 0.5 * s;
+    s = lane63_sum(s);
+    if ((threadIdx.x & 63) == 63) phi[q] = 0.5 * s;
 }
 
 int launch_loglik(mls2mc_ctx* ctx, int64_t N, const double* G, const double* y, double* phi,
                   hipStream_t s)
 {
     if (N == 0) return MLS2MC_OK;
-    loglik_kernel<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(N, ctx->nobs, G, y,
-                                                             1.0 / ctx->prob.sigma_n, phi);
+    loglik_kernel<<<(unsigned)((N + 3) / 4), 256, 0, s>>>(N, ctx->nobs, G, y, 1.0 / ctx->prob.sigma_n, phi);
     MLS_CHECK_HIP(hipGetLastError());
     return MLS2MC_OK;
 }
 
 // ------------------------------------------------------------ next step --
-// One workgroup.  lw_j(t) = (-t*scale) d_j; its maximum is attained at
-// min_j d_j (the factor is <= 0 and rounding is monotone), so one minimum
-// serves every bisection step.  ESS(t) = (sum e^{lw-m})^2 / sum e^{2(lw-m)}.
+// lw_j(t) = (-t*scale) d_j; its maximum is attained at min_j d_j (the factor
+// is <= 0 and rounding is monotone), so one minimum serves every bisection
+// step.  ESS(t) = (sum e^{lw-m})^2 / sum e^{2(lw-m)}.  The 64 bisection steps
+// are a serial chain of evaluations, so what bounds the step is the latency
+// of one evaluation, not its arithmetic:
+//  * up to kStepSmall particles one workgroup keeps d in registers and an
+//    evaluation is one exponential per element and one barrier (both sums
+//    reduced by DPP together; 130 us -> 27 us at N = 200, where four barriers
+//    and shuffles took 2 us per evaluation);
+//  * beyond, a launch evaluates all midpoints of the next L bisection levels
+//    (2^L - 1, every one by its own workgroups) and the next launch walks
+//    down them: 64 / L launches instead of 64 passes of one workgroup
+//    (474 us -> 76 us at N = 16384: 11 launches of 6.2 us).
+// Both take the midpoints and the comparisons of plain bisection.
 constexpr int kNS = 1024;
+constexpr int64_t kStepSmall = 2048;
 
-__device__ double ess_eval(int64_t N, const double* __restrict__ d, double dmin, double scale,
-                           double t, double* red)
+struct StepIn {
+    int64_t N;
+    const double* d;
+    double scale, cur, tau, eps;
+    double *out3, *logw, *w;
+};
+
+// {sum a, sum b} over the workgroup in every thread; red: two buffers of one
+// entry per wave, used in turn so that one barrier serves
+template <int BS>
+__device__ __forceinline__ double2 pair_sum(double a, double b, double2 (*red)[BS / 64], int& turn)
 {
-    const double a = -t * scale;
-    const double m = a * dmin;
-    double s1 = 0.0, s2 = 0.0;
-    for (int64_t j = threadIdx.x; j < N; j += kNS) {
-        const double v = exp(a * d[j] - m);
-        s1 += v;
-        s2 += v * v;
+    a = lane63_sum(a);
+    b = lane63_sum(b);
+    double2* r = red[turn];
+    turn ^= 1;
+    if ((threadIdx.x & 63) == 63) r[threadIdx.x >> 6] = make_double2(a, b);
+    __syncthreads();
+    double2 s = r[0];
+#pragma unroll
+    for (int k = 1; k < BS / 64; ++k) {
+        s.x += r[k].x;
+        s.y += r[k].y;
     }
-    s1 = block_sum<kNS>(s1, red);
-    s2 = block_sum<kNS>(s2, red);
-    return s1 * s1 / s2;
+    return make_double2(wave_uniform(s.x), wave_uniform(s.y));
 }
 
-__global__ __launch_bounds__(kNS) void next_step_kernel(int64_t N, const double* __restrict__ d,
-                                                        double scale, double cur, double tau,
-                                                        double eps, double* __restrict__ out3,
-                                                        double* __restrict__ logw,
-                                                        double* __restrict__ w)
+template <int BS, int PER>
+__global__ __launch_bounds__(BS) void next_step_small_kernel(StepIn A)
 {
-    __shared__ double red[kNS / 64];
+    __shared__ double red1[BS / 64];
+    __shared__ double2 red[2][BS / 64];
+    double d[PER];
     double dmin = INFINITY;
     int bad = 0;
-    for (int64_t j = threadIdx.x; j < N; j += kNS) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t j = threadIdx.x + k * BS;
+        d[k] = j < A.N ? A.d[j] : INFINITY;  // an infinite difference weighs nothing below
+        if (j < A.N && !isfinite(d[k])) bad = 1;
+        dmin = fmin(dmin, d[k]);
+    }
+    dmin = -block_max<BS>(-dmin, red1);
+    if (__syncthreads_or(bad)) {
+        if (threadIdx.x == 0) A.out3[0] = A.out3[1] = A.out3[2] = NAN;
+        return;
+    }
+    int turn = 0;
+    double2 s;
+    auto ess = [&](double t) {
+        const double a = -t * A.scale;
+        const double m = a * dmin;
+        double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const double v = threadIdx.x + k * BS < A.N ? exp(a * d[k] - m) : 0.0;
+            s1 += v;
+            s2 += v * v;
+        }
+        s = pair_sum<BS>(s1, s2, red, turn);
+        return s.x * s.x / s.y;
+    };
+    const double tmax = 1.0 - A.cur;
+    const double tmin = A.eps < tmax ? A.eps : tmax;
+    double t, e;
+    bool at_end = false;
+    if ((e = ess(tmax)) >= A.tau) {
+        t = tmax;
+        at_end = true;
+    } else if ((e = ess(tmin)) <= A.tau) {
+        t = tmin;
+        at_end = (tmin == tmax);
+    } else {
+        double lo = tmin, hi = tmax, elo = e;
+        double2 slo = s;
+        for (int it = 0; it < 64; ++it) {
+            const double mid = 0.5 * (lo + hi);
+            if (mid == lo || mid == hi) break;  // adjacent: the remaining steps change nothing
+            const double em = ess(mid);
+            if (em >= A.tau) {
+                lo = mid;
+                elo = em;
+                slo = s;
+            } else {
+                hi = mid;
+            }
+        }
+        t = lo;
+        e = elo;
+        s = slo;
+    }
+    const double a = -t * A.scale;
+    const double lse = a * dmin + log(s.x);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int64_t j = threadIdx.x + k * BS;
+        if (j >= A.N) break;
+        const double lw = a * d[k];
+        if (A.logw) A.logw[j] = lw;
+        if (A.w) A.w[j] = exp(lw - lse);
+    }
+    if (threadIdx.x == 0) {
+        A.out3[0] = at_end ? 1.0 : A.cur + t;
+        A.out3[1] = lse - log((double)A.N);
+        A.out3[2] = e;
+    }
+}
+
+// Scratch of the many-workgroup step, kept by the context: per-block minima,
+// the state of the search before each round, and two buffers of partial sums
+// [candidate][chunk].
+enum { SS_LO, SS_HI, SS_S1, SS_S2, SS_DMIN, SS_MODE, SS_LEN = 8 };
+enum { STEP_SEARCH = 0, STEP_DONE = 1, STEP_END = 2, STEP_BAD = 3 };
+constexpr int kStepMin = 256;        // blocks of the minimum
+constexpr int kStepParts = 576;      // most partial sums of a round
+constexpr int kStepCand = 129;       // most candidates of a round
+struct StepScratch {
+    double minima[kStepMin];
+    double state[68][SS_LEN];
+    double2 part[2][kStepParts];
+};
+static_assert(sizeof(StepScratch) <= kStepScratchBytes, "the context's step scratch");
+
+__global__ __launch_bounds__(256) void step_min_kernel(int64_t N, const double* __restrict__ d, StepScratch* S)
+{
+    __shared__ double red[4];
+    double dmin = INFINITY;
+    int bad = 0;
+    for (int64_t j = blockIdx.x * 256 + threadIdx.x; j < N; j += gridDim.x * 256) {
         const double v = d[j];
         if (!isfinite(v)) bad = 1;
         dmin = fmin(dmin, v);
     }
-    dmin = -block_max<kNS>(-dmin, red);
-    const double nbad = block_sum<kNS>((double)bad, red);
-    if (nbad > 0.0) {
-        if (threadIdx.x == 0) out3[0] = out3[1] = out3[2] = NAN;
-        return;
+    dmin = -block_max<256>(-dmin, red);
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) S->minima[blockIdx.x] = bad ? NAN : dmin;
+}
+
+struct StepState {
+    double lo, hi, s1, s2, dmin;
+    int mode;
+};
+
+// The search's state before round r (each of L levels): the state before
+// round r - 1 advanced by that round's sums.  Every workgroup forms it for
+// itself; e, s1 and s2 are LDS arrays of kStepCand entries.  nmin: blocks of
+// the minimum; levels: bisection levels of round r - 1.
+template <int BS>
+__device__ StepState step_state(const StepIn& A, const StepScratch* S, int r, int nmin, int L, int levels, int chunks,
+                                double* e, double* s1, double* s2)
+{
+    __shared__ double red[BS / 64];
+    StepState st;
+    const double tmax = 1.0 - A.cur;
+    const double tmin = A.eps < tmax ? A.eps : tmax;
+    if (r == 0) {
+        double m = INFINITY;
+        int bad = 0;
+        for (int k = threadIdx.x; k < nmin; k += BS) {
+            const double v = S->minima[k];
+            if (isnan(v)) bad = 1;
+            m = fmin(m, v);
+        }
+        st.dmin = -block_max<BS>(-m, red);
+        st.mode = __syncthreads_or(bad) ? STEP_BAD : STEP_SEARCH;
+        st.lo = tmin;
+        st.hi = tmax;
+        st.s1 = st.s2 = 0.0;
+        return st;
     }
-    const double tmax = 1.0 - cur;
-    const double tmin = eps < tmax ? eps : tmax;
+    const double* p = S->state[r - 1];
+    st.lo = p[SS_LO]; st.hi = p[SS_HI]; st.s1 = p[SS_S1]; st.s2 = p[SS_S2]; st.dmin = p[SS_DMIN];
+    st.mode = (int)p[SS_MODE];
+    if (st.mode != STEP_SEARCH) return st;
+    const int n = r == 1 ? (1 << L) + 1 : 1 << levels;
+    const double2* part = S->part[(r - 1) & 1];
+    for (int c = threadIdx.x; c < n; c += BS) {
+        double a = 0.0, b = 0.0;
+        for (int k = 0; k < chunks; ++k) {
+            a += part[c * chunks + k].x;
+            b += part[c * chunks + k].y;
+        }
+        s1[c] = a;
+        s2[c] = b;
+        e[c] = a * a / b;
+    }
+    __syncthreads();
+    auto take = [&](int c) { st.s1 = s1[c]; st.s2 = s2[c]; };
+    if (r == 1) {  // the first round also took both ends: 0 is tmax, 1 << L is tmin
+        if (e[0] >= A.tau) {
+            st.lo = tmax;
+            take(0);
+            st.mode = STEP_END;
+            return st;
+        }
+        take(1 << L);
+        if (e[1 << L] <= A.tau) {
+            st.mode = tmin == tmax ? STEP_END : STEP_DONE;
+            return st;
+        }
+    }
+    int node = 1;
+    for (int k = 0; k < levels; ++k) {
+        const double mid = 0.5 * (st.lo + st.hi);
+        if (e[node] >= A.tau) {
+            st.lo = mid;
+            take(node);
+            node = 2 * node + 1;
+        } else {
+            st.hi = mid;
+            node = 2 * node;
+        }
+    }
+    return st;
+}
+
+// Round r: candidate blockIdx.x (the heap index of a midpoint; in the first
+// round also the two ends), chunk blockIdx.y of the particles.
+__global__ __launch_bounds__(256) void step_round_kernel(StepIn A, StepScratch* S, int r, int nmin, int L, int prev,
+                                                         int levels, int64_t chunk)
+{
+    __shared__ double e[kStepCand], s1[kStepCand], s2[kStepCand];
+    __shared__ double2 red[2][4];
+    const StepState st = step_state<256>(A, S, r, nmin, L, prev, gridDim.y, e, s1, s2);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        double* p = S->state[r];
+        p[SS_LO] = st.lo; p[SS_HI] = st.hi; p[SS_S1] = st.s1; p[SS_S2] = st.s2; p[SS_DMIN] = st.dmin;
+        p[SS_MODE] = (double)st.mode;
+    }
+    if (st.mode != STEP_SEARCH) return;
+    const int c = r == 0 ? blockIdx.x : blockIdx.x + 1;
     double t;
-    bool at_end = false;
-    if (ess_eval(N, d, dmin, scale, tmax, red) >= tau) {
-        t = tmax;
-        at_end = true;
-    } else if (ess_eval(N, d, dmin, scale, tmin, red) <= tau) {
-        t = tmin;
-        at_end = (tmin == tmax);
+    if (r == 0 && c == 0) {
+        t = st.hi;
+    } else if (r == 0 && c == 1 << L) {
+        t = st.lo;
     } else {
-        double lo = tmin, hi = tmax;
-        for (int it = 0; it < 64; ++it) {
+        double lo = st.lo, hi = st.hi;
+        for (int bit = 30 - __builtin_clz(c); bit >= 0; --bit) {
             const double mid = 0.5 * (lo + hi);
-            if (ess_eval(N, d, dmin, scale, mid, red) >= tau) lo = mid;
+            if ((c >> bit) & 1) lo = mid;
             else hi = mid;
         }
-        t = lo;
+        t = 0.5 * (lo + hi);
     }
-    const double a = -t * scale;
-    const double m = a * dmin;
-    double s = 0.0;
-    for (int64_t j = threadIdx.x; j < N; j += kNS) s += exp(a * d[j] - m);
-    s = block_sum<kNS>(s, red);
-    const double lse = m + log(s);
-    for (int64_t j = threadIdx.x; j < N; j += kNS) {
-        const double lw = a * d[j];
-        if (logw) logw[j] = lw;
-        if (w) w[j] = exp(lw - lse);
+    const double a = -t * A.scale;
+    const double m = a * st.dmin;
+    double v1 = 0.0, v2 = 0.0;
+    const int64_t j0 = blockIdx.y * chunk, j1 = j0 + chunk < A.N ? j0 + chunk : A.N;
+    for (int64_t j = j0 + threadIdx.x; j < j1; j += 256) {
+        const double v = exp(a * A.d[j] - m);
+        v1 += v;
+        v2 += v * v;
     }
-    const double e = ess_eval(N, d, dmin, scale, t, red);
-    if (threadIdx.x == 0) {
-        out3[0] = at_end ? 1.0 : cur + t;
-        out3[1] = lse - log((double)N);
-        out3[2] = e;
+    int turn = 0;
+    const double2 s = pair_sum<256>(v1, v2, red, turn);
+    if (threadIdx.x == 0) S->part[r & 1][c * gridDim.y + blockIdx.y] = s;
+}
+
+__global__ __launch_bounds__(256) void step_out_kernel(StepIn A, const StepScratch* S, int r, int L, int prev,
+                                                       int chunks)
+{
+    __shared__ double e[kStepCand], s1[kStepCand], s2[kStepCand];
+    const StepState st = step_state<256>(A, S, r, 0, L, prev, chunks, e, s1, s2);
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (st.mode == STEP_BAD) {
+        if (first) A.out3[0] = A.out3[1] = A.out3[2] = NAN;
+        return;
+    }
+    const double t = st.lo;
+    const double a = -t * A.scale;
+    const double lse = a * st.dmin + log(st.s1);
+    for (int64_t j = blockIdx.x * (int64_t)256 + threadIdx.x; j < A.N; j += gridDim.x * (int64_t)256) {
+        const double lw = a * A.d[j];
+        if (A.logw) A.logw[j] = lw;
+        if (A.w) A.w[j] = exp(lw - lse);
+    }
+    if (first) {
+        A.out3[0] = st.mode == STEP_END ? 1.0 : A.cur + t;
+        A.out3[1] = lse - log((double)A.N);
+        A.out3[2] = st.s1 * st.s1 / st.s2;
     }
 }
 
-int launch_next_step(mls2mc_ctx*, int64_t N, const double* d, double scale, double cur, double tau,
+int launch_next_step(mls2mc_ctx* ctx, int64_t N, const double* d, double scale, double cur, double tau,
                      double eps, double* out3, double* logw, double* w, hipStream_t s)
 {
-    next_step_kernel<<<1, kNS, 0, s>>>(N, d, scale, cur, tau, eps, out3, logw, w);
+    const StepIn A{N, d, scale, cur, tau, eps, out3, logw, w};
+    if (N <= kStepSmall) {
+        if (N <= 256) next_step_small_kernel<256, 1><<<1, 256, 0, s>>>(A);
+        else if (N <= 512) next_step_small_kernel<512, 1><<<1, 512, 0, s>>>(A);
+        else if (N <= 1024) next_step_small_kernel<512, 2><<<1, 512, 0, s>>>(A);
+        else next_step_small_kernel<1024, 2><<<1, 1024, 0, s>>>(A);
+        MLS_CHECK_HIP(hipGetLastError());
+        return MLS2MC_OK;
+    }
+    // Levels per round: a round costs its launch (about 4 us) plus 2^L N
+    // exponentials; the more particles, the fewer midpoints pay.  About 512
+    // workgroups per round.
+    const int L = N <= 8192 ? 7 : N <= 65536 ? 6 : N <= (1 << 18) ? 5 : N <= (1 << 20) ? 4 : 3;
+    const int chunks = 512 >> L;
+    const int64_t chunk = (N + chunks - 1) / chunks;
+    const int nmin = (int)std::min<int64_t>(kStepMin, (N + 1023) / 1024);
+    StepScratch* S = step_scratch(ctx);
+    step_min_kernel<<<nmin, 256, 0, s>>>(N, d, S);
+    int r = 0, prev = 0;
+    for (int done = 0; done < 64; ++r) {
+        const int levels = std::min(L, 64 - done);
+        const unsigned cand = r == 0 ? (1u << L) + 1 : (1u << levels) - 1;
+        step_round_kernel<<<dim3(cand, chunks), 256, 0, s>>>(A, S, r, nmin, L, prev, levels, chunk);
+        prev = levels;
+        done += levels;
+    }
+    step_out_kernel<<<(unsigned)std::min<int64_t>(1024, (N + 255) / 256), 256, 0, s>>>(A, S, r, L, prev, chunks);
     MLS_CHECK_HIP(hipGetLastError());
     return MLS2MC_OK;
 }
@@ -137,21 +389,21 @@ __global__ __launch_bounds__(kNS) void ess_diff_kernel(int64_t N, const double* 
         mx = fmax(mx, a * v);
     }
     mx = block_max<kNS>(mx, red);
-    const double nbad = block_sum<kNS>((double)bad, red);
-    if (nbad > 0.0) {
+    if (__syncthreads_or(bad)) {
         if (threadIdx.x == 0) out[0] = out[1] = NAN;
         return;
     }
+    __shared__ double2 red2[2][kNS / 64];
     double s1 = 0.0, s2 = 0.0;
     for (int64_t j = threadIdx.x; j < N; j += kNS) {
         const double v = exp(a * (dlo ? dhi[j] - dlo[j] : dhi[j]) - mx);
         s1 += v;
         s2 += v * v;
     }
-    s1 = block_sum<kNS>(s1, red);
-    s2 = block_sum<kNS>(s2, red);
+    int turn = 0;
+    const double2 s = pair_sum<kNS>(s1, s2, red2, turn);
     if (threadIdx.x == 0) {
-        const double e = s1 * s1 / s2;
+        const double e = s.x * s.x / s.y;
         out[0] = e;
         out[1] = (double)N / e - 1.0;
     }
@@ -218,77 +470,230 @@ int launch_linear_map(int64_t N, int K, int nobs, const double* S, const double*
 }
 
 // ------------------------------------------------------------- resample --
-// Exact integer CDF (see mls2mc.h).  One workgroup; thread k owns the
-// contiguous chunk [k N / BS, (k+1) N / BS) for the quantised prefix sums.
-__global__ __launch_bounds__(kNS) void resample_kernel(int64_t N, const double* __restrict__ w,
-                                                       const double* __restrict__ u,
-                                                       uint64_t* __restrict__ C,
-                                                       int32_t* __restrict__ anc)
+// Exact integer CDF (see mls2mc.h): every sum is of integers, so any split
+// gives the same ancestors.  Up to kResSmall particles one workgroup does it
+// all with the prefix sums in LDS; beyond, blocks of kResBlock particles form
+// their maxima, their quantised totals, the prefix sums and the searches in
+// four launches.  (us, one workgroup with a serial scan of its 1024 chunk
+// totals and searches in global memory -> now: N = 200 17 -> 4, N = 16384
+// 146 -> 22.)
+constexpr int64_t kResSmall = 4096;
+constexpr int kResBlock = 4096;
+
+__device__ __forceinline__ bool bad_weight(double v) { return !(v >= 0.0) || isinf(v); }
+__device__ __forceinline__ bool bad_uniform(double v) { return !(v >= 0.0 && v < 1.0); }
+// q_j = floor(w_j 2^(62 - c) / 2^ex): ex brings max w into [1/2, 1), c = ceil(log2 N)
+__device__ __forceinline__ uint64_t quantised(double w, int ex, int c)
 {
-    __shared__ double red[kNS / 64];
-    __shared__ uint64_t part[kNS];
-    double mx = 0.0;
+    return (uint64_t)floor(ldexp(ldexp(w, -ex), 62 - c));
+}
+__device__ __forceinline__ int ceil_log2(int64_t N) { return N <= 1 ? 0 : 64 - __builtin_clzll((uint64_t)(N - 1)); }
+// floor(u 2^53 T / 2^53)
+__device__ __forceinline__ uint64_t target(double u, uint64_t T)
+{
+    const uint64_t U = (uint64_t)ldexp(u, 53);
+    const uint64_t ph = __umul64hi(U, T), pl = U * T;
+    return (ph << 11) | (pl >> 53);
+}
+
+// inclusive sum of v over the workgroup's threads in order; part: one entry
+// per wave.  *total: the sum over all threads.
+template <int BS>
+__device__ __forceinline__ uint64_t scan_u64(uint64_t v, uint64_t* part, uint64_t* total)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t n = __shfl_up((unsigned long long)v, o, 64);
+        if (lane >= o) v += n;
+    }
+    if (lane == 63) part[wv] = v;
+    __syncthreads();
+    uint64_t before = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < BS / 64; ++k) {
+        if (k < wv) before += part[k];
+        all += part[k];
+    }
+    *total = all;
+    return v + before;
+}
+
+template <int BS, int PER>
+__global__ __launch_bounds__(BS) void resample_small_kernel(int N, const double* __restrict__ w,
+                                                            const double* __restrict__ u,
+                                                            int32_t* __restrict__ anc)
+{
+    __shared__ double red[BS / 64];
+    __shared__ uint64_t part[BS / 64];
+    __shared__ uint64_t C[BS * PER];
+    double wv[PER], uv[PER], mx = 0.0;
     int bad = 0;
-    for (int64_t j = threadIdx.x; j < N; j += kNS) {
-        const double v = w[j];
-        if (!(v >= 0.0) || isinf(v)) bad = 1;
-        else mx = fmax(mx, v);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int j = threadIdx.x * PER + k, i = threadIdx.x + k * BS;
+        wv[k] = j < N ? w[j] : 0.0;
+        uv[k] = i < N ? u[i] : 0.0;
+        if (bad_weight(wv[k]) || bad_uniform(uv[k])) bad = 1;
+        else mx = fmax(mx, wv[k]);
     }
-    for (int64_t i = threadIdx.x; i < N; i += kNS) {
-        const double v = u[i];
-        if (!(v >= 0.0 && v < 1.0)) bad = 1;
-    }
-    mx = block_max<kNS>(mx, red);
-    const double nbad = block_sum<kNS>((double)bad, red);
-    if (nbad > 0.0 || !(mx > 0.0)) {
-        for (int64_t i = threadIdx.x; i < N; i += kNS) anc[i] = -1;
+    mx = block_max<BS>(mx, red);
+    if (__syncthreads_or(bad) || !(mx > 0.0)) {
+        for (int i = threadIdx.x; i < N; i += BS) anc[i] = -1;
         return;
     }
     int ex;
     frexp(mx, &ex);
-    int c = 0;
-    while ((int64_t(1) << c) < N) ++c;
-    const int64_t lo = (int64_t)threadIdx.x * N / kNS, hi = (int64_t)(threadIdx.x + 1) * N / kNS;
-    uint64_t run = 0;
-    for (int64_t j = lo; j < hi; ++j) {
-        run += (uint64_t)floor(ldexp(ldexp(w[j], -ex), 62 - c));
-        C[j] = run;
+    const int c = ceil_log2(N);
+    uint64_t run[PER], sum = 0, T;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        sum += quantised(wv[k], ex, c);
+        run[k] = sum;
     }
-    part[threadIdx.x] = run;
+    const uint64_t before = scan_u64<BS>(sum, part, &T) - sum;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) C[threadIdx.x * PER + k] = before + run[k];  // past N: T, never below a target
     __syncthreads();
-    if (threadIdx.x == 0) {  // exclusive scan of the chunk totals (exact integers)
-        uint64_t acc = 0;
-        for (int k = 0; k < kNS; ++k) {
-            const uint64_t v = part[k];
-            part[k] = acc;
-            acc += v;
-        }
-    }
-    __syncthreads();
-    const uint64_t off = part[threadIdx.x];
-    for (int64_t j = lo; j < hi; ++j) C[j] += off;
-    __syncthreads();
-    __threadfence_block();
-    const uint64_t T = C[N - 1];
-    for (int64_t i = threadIdx.x; i < N; i += kNS) {
-        const uint64_t U = (uint64_t)ldexp(u[i], 53);
-        const uint64_t ph = __umul64hi(U, T), pl = U * T;
-        const uint64_t ti = (ph << 11) | (pl >> 53);
-        int64_t a = 0, b = N - 1;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = threadIdx.x + k * BS;
+        if (i >= N) break;
+        const uint64_t ti = target(uv[k], T);
+        int a = 0, b = N - 1;
         while (a < b) {
-            const int64_t mid = a + (b - a) / 2;
+            const int mid = (a + b) >> 1;
             if (C[mid] > ti) b = mid; else a = mid + 1;
         }
-        anc[i] = (int32_t)a;
+        anc[i] = a;
     }
 }
 
-// C: N uint64 of scratch for the prefix sums (every entry is written before
-// it is read, so it needs no clearing)
+// per block: the largest weight, or -1 when a weight or uniform is invalid
+__global__ __launch_bounds__(1024) void resample_max_kernel(int64_t N, const double* __restrict__ w,
+                                                            const double* __restrict__ u, double* __restrict__ pm)
+{
+    __shared__ double red[16];
+    double mx = 0.0;
+    int bad = 0;
+    const int64_t j0 = blockIdx.x * (int64_t)kResBlock;
+#pragma unroll
+    for (int k = 0; k < kResBlock / 1024; ++k) {
+        const int64_t j = j0 + threadIdx.x + 1024 * k;
+        if (j >= N) break;
+        const double v = w[j];
+        if (bad_weight(v) || bad_uniform(u[j])) bad = 1;
+        else mx = fmax(mx, v);
+    }
+    mx = block_max<1024>(mx, red);
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) pm[blockIdx.x] = bad ? -1.0 : mx;
+}
+
+// per block: its quantised total; the first block also notes the largest
+// weight (0 when nothing can be drawn) in pm[gridDim.x]
+__global__ __launch_bounds__(1024) void resample_total_kernel(int64_t N, const double* __restrict__ w,
+                                                              double* __restrict__ pm, uint64_t* __restrict__ ps)
+{
+    __shared__ double red[16];
+    __shared__ uint64_t part[16];
+    double mx = 0.0;
+    int bad = 0;
+    for (unsigned k = threadIdx.x; k < gridDim.x; k += 1024) {
+        const double v = pm[k];
+        if (v < 0.0) bad = 1;
+        mx = fmax(mx, v);
+    }
+    mx = block_max<1024>(mx, red);
+    if (__syncthreads_or(bad)) mx = 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) pm[gridDim.x] = mx;
+    if (!(mx > 0.0)) return;
+    int ex;
+    frexp(mx, &ex);
+    const int c = ceil_log2(N);
+    uint64_t sum = 0, T;
+    const int64_t j0 = blockIdx.x * (int64_t)kResBlock;
+#pragma unroll
+    for (int k = 0; k < kResBlock / 1024; ++k) {
+        const int64_t j = j0 + threadIdx.x + 1024 * k;
+        if (j < N) sum += quantised(w[j], ex, c);
+    }
+    (void)scan_u64<1024>(sum, part, &T);
+    if (threadIdx.x == 0) ps[blockIdx.x] = T;
+}
+
+__global__ __launch_bounds__(1024) void resample_prefix_kernel(int64_t N, const double* __restrict__ w,
+                                                               const double* __restrict__ pm,
+                                                               const uint64_t* __restrict__ ps,
+                                                               uint64_t* __restrict__ C)
+{
+    __shared__ uint64_t part[2][16];
+    const double mx = pm[gridDim.x];
+    if (!(mx > 0.0)) return;
+    uint64_t sum = 0, T, before;
+    for (unsigned k = threadIdx.x; k < blockIdx.x; k += 1024) sum += ps[k];
+    (void)scan_u64<1024>(sum, part[0], &before);
+    int ex;
+    frexp(mx, &ex);
+    const int c = ceil_log2(N);
+    constexpr int PER = kResBlock / 1024;
+    const int64_t j0 = blockIdx.x * (int64_t)kResBlock + threadIdx.x * PER;
+    uint64_t run[PER];
+    sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (j0 + k < N) sum += quantised(w[j0 + k], ex, c);
+        run[k] = sum;
+    }
+    before += scan_u64<1024>(sum, part[1], &T) - sum;
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+        if (j0 + k < N) C[j0 + k] = before + run[k];
+}
+
+__global__ __launch_bounds__(256) void resample_search_kernel(int64_t N, const double* __restrict__ u,
+                                                              const double* __restrict__ mx,
+                                                              const uint64_t* __restrict__ C,
+                                                              int32_t* __restrict__ anc)
+{
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i >= N) return;
+    if (!(*mx > 0.0)) {
+        anc[i] = -1;
+        return;
+    }
+    const uint64_t ti = target(u[i], C[N - 1]);
+    int64_t a = 0, b = N - 1;
+    while (a < b) {
+        const int64_t mid = a + (b - a) / 2;
+        if (C[mid] > ti) b = mid; else a = mid + 1;
+    }
+    anc[i] = (int32_t)a;
+}
+
+int64_t resample_scratch(int64_t N)
+{
+    return N <= kResSmall ? 1 : N + 2 * ((N + kResBlock - 1) / kResBlock) + 1;
+}
+
+// C: resample_scratch(N) uint64 of scratch (every entry is written before it
+// is read, so it needs no clearing)
 int launch_resample_into(int64_t N, const double* w, const double* u, uint64_t* C, int32_t* anc,
                          hipStream_t s)
 {
-    resample_kernel<<<1, kNS, 0, s>>>(N, w, u, C, anc);
+    if (N <= kResSmall) {
+        if (N <= 256) resample_small_kernel<256, 1><<<1, 256, 0, s>>>((int)N, w, u, anc);
+        else if (N <= 1024) resample_small_kernel<1024, 1><<<1, 1024, 0, s>>>((int)N, w, u, anc);
+        else resample_small_kernel<1024, 4><<<1, 1024, 0, s>>>((int)N, w, u, anc);
+    } else {
+        const unsigned nb = (unsigned)((N + kResBlock - 1) / kResBlock);
+        uint64_t* ps = C + N;
+        double* pm = reinterpret_cast<double*>(ps + nb);
+        resample_max_kernel<<<nb, 1024, 0, s>>>(N, w, u, pm);
+        resample_total_kernel<<<nb, 1024, 0, s>>>(N, w, pm, ps);
+        resample_prefix_kernel<<<nb, 1024, 0, s>>>(N, w, pm, ps, C);
+        resample_search_kernel<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(N, u, pm + nb, C, anc);
+    }
     MLS_CHECK_HIP(hipGetLastError());
     return MLS2MC_OK;
 }
@@ -296,7 +701,7 @@ int launch_resample_into(int64_t N, const double* w, const double* u, uint64_t* 
 int launch_resample(mls2mc_ctx* ctx, int64_t N, const double* w, const double* u, int32_t* anc,
                     hipStream_t s)
 {
-    MLS_TRY(ctx->ws_misc.ensure(sizeof(uint64_t) * (size_t)N));
+    MLS_TRY(ctx->ws_misc.ensure(sizeof(uint64_t) * (size_t)resample_scratch(N)));
     return launch_resample_into(N, w, u, ctx->ws_misc.as<uint64_t>(), anc, s);
 }
 
@@ -396,16 +801,17 @@ int launch_pcn_propose(int64_t N, int K, double s_pcn, int kernel, const double*
 // mode 0: tempering (Psi = beta Phi_lo); 1: bridging with zeta < 1; 2:
 // bridging at zeta = 1 (Psi = beta Phi_hi).  rwm: the random-walk kernel,
 // whose ratio also carries the N(0, I) prior term |theta|^2 / 2.
-__global__ void pcn_accept_kernel(int64_t N, int K, int nobs, int mode, int rwm, double beta, double zeta,
-                                  const double* __restrict__ u, const double* __restrict__ thn,
-                                  const double* __restrict__ Gln, const double* __restrict__ Ghn,
-                                  const double* __restrict__ pln, const double* __restrict__ phn,
-                                  const int8_t* __restrict__ stl, const int8_t* __restrict__ sth,
-                                  double* __restrict__ th, double* __restrict__ Gl,
-                                  double* __restrict__ Gh, double* __restrict__ pl,
-                                  double* __restrict__ ph, uint8_t* __restrict__ acc)
+// One wave per particle, so that rows are copied by neighbouring lanes (one
+// thread per particle copying its rows took 15 us at N = 1000, K = 50).
+__global__ __launch_bounds__(256) void pcn_accept_kernel(
+    int64_t N, int K, int nobs, int mode, int rwm, double beta, double zeta, const double* __restrict__ u,
+    const double* __restrict__ thn, const double* __restrict__ Gln, const double* __restrict__ Ghn,
+    const double* __restrict__ pln, const double* __restrict__ phn, const int8_t* __restrict__ stl,
+    const int8_t* __restrict__ sth, double* __restrict__ th, double* __restrict__ Gl, double* __restrict__ Gh,
+    double* __restrict__ pl, double* __restrict__ ph, uint8_t* __restrict__ acc)
 {
-    const int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t j = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     if (j >= N) return;
     const bool need_lo = mode != 2, need_hi = mode != 0;
     double psi_old, psi_new;
@@ -421,29 +827,29 @@ __global__ void pcn_accept_kernel(int64_t N, int K, int nobs, int mode, int rwm,
     }
     if (rwm) {
         double qo = 0.0, qn = 0.0;
-        for (int k = 0; k < K; ++k) {
+        for (int k = lane; k < K; k += 64) {
             qo += th[j * K + k] * th[j * K + k];
             qn += thn[j * K + k] * thn[j * K + k];
         }
-        psi_old += 0.5 * qo;
-        psi_new += 0.5 * qn;
+        psi_old += 0.5 * wave_sum(qo);
+        psi_new += 0.5 * wave_sum(qn);
     }
     bool ok = true;
     if (need_lo && stl && stl[j] != 0) ok = false;
     if (need_hi && sth && sth[j] != 0) ok = false;
     const bool a = ok && (log(u[j]) < -(psi_new - psi_old));
     if (a) {
-        for (int k = 0; k < K; ++k) th[j * K + k] = thn[j * K + k];
-        if (need_lo) {
-            for (int o = 0; o < nobs; ++o) Gl[j * nobs + o] = Gln[j * nobs + o];
-            pl[j] = pln[j];
-        }
-        if (need_hi) {
-            for (int o = 0; o < nobs; ++o) Gh[j * nobs + o] = Ghn[j * nobs + o];
-            ph[j] = phn[j];
-        }
+        for (int k = lane; k < K; k += 64) th[j * K + k] = thn[j * K + k];
+        if (need_lo)
+            for (int o = lane; o < nobs; o += 64) Gl[j * nobs + o] = Gln[j * nobs + o];
+        if (need_hi)
+            for (int o = lane; o < nobs; o += 64) Gh[j * nobs + o] = Ghn[j * nobs + o];
     }
-    if (acc) acc[j] = a ? 1 : 0;
+    if (lane == 0) {
+        if (a && need_lo) pl[j] = pln[j];
+        if (a && need_hi) ph[j] = phn[j];
+        if (acc) acc[j] = a ? 1 : 0;
+    }
 }
 
 int launch_pcn_accept(int64_t N, int K, int nobs, int mode, int rwm, double beta, double zeta,
@@ -453,7 +859,7 @@ int launch_pcn_accept(int64_t N, int K, int nobs, int mode, int rwm, double beta
                       double* Ghi, double* plo, double* phi, uint8_t* acc, hipStream_t s)
 {
     if (N == 0) return MLS2MC_OK;
-    pcn_accept_kernel<<<(unsigned)((N + 255) / 256), 256, 0, s>>>(
+    pcn_accept_kernel<<<(unsigned)((N + 3) / 4), 256, 0, s>>>(
         N, K, nobs, mode, rwm, beta, zeta, u, th_new, Glo_new, Ghi_new, plo_new, phi_new, st_lo, st_hi,
         theta, Glo, Ghi, plo, phi, acc);
     MLS_CHECK_HIP(hipGetLastError());
