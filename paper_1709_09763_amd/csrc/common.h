@@ -178,7 +178,7 @@ struct SolveItem {
     int32_t* iters;      // N or null
 };
 int launch_solve_list(mls2mc_ctx* ctx, const SolveItem* items_dev, int n_items, int64_t total, int lmax,
-                      bool mixed, hipStream_t s);
+                      bool walked, bool mixed, hipStream_t s);
 
 // one entry of a grouped KL GEMM launch (64 x 64 output tiles)
 struct GemmItem {
@@ -207,12 +207,17 @@ struct ListLevel {  // the items of one level that the resident solver takes
     int l, first, n;
     int64_t total;
 };
+struct ListGroup {  // the items of one work-list launch
+    int first = 0, n = 0;
+    int64_t total = 0;
+    int lmax = 0;
+};
 struct ListChunk {  // one prepared grouped GEMM and the solves of its items
     const GemmItem* gemm;
-    const SolveItem* solve;  // the first n_list of n: the work-list kernel's
-    int n, n_list;
-    int64_t tiles, total;    // total: particles of the work-list kernel's items
-    int lmax;
+    const SolveItem* solve;
+    int n;
+    int64_t tiles;
+    ListGroup group[2];  // work-list launches: the walked levels on their own, the others
     std::vector<ListLevel> levels;
 };
 int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items, std::vector<ListChunk>& out, hipStream_t s);

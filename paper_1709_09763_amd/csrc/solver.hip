@@ -1514,7 +1514,11 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_kernel(SolveParams P
 // One persistent launch over the particles of many (instance, level)
 // items: particle p belongs to the item whose prefix range holds p; items
 // are ordered by level, finest first, so the costliest particles start
-// first.  Slots are sized for the finest level in the list.
+// first, and the particles are handed out one at a time as in
+// solve_kernel.  Slots are sized for the finest level in the list.  WK = 2:
+// every item is of h = 1/256 or finer and runs the fused row walks (the
+// separate passes beside them in one kernel, inlined or called, cost it
+// hundreds of spilled registers).
 struct ListParams {
     const SolveItem* items;
     int n_items;
@@ -1526,6 +1530,7 @@ struct ListParams {
     int64_t lds_elems;
     int cinv_lds;
     int64_t ring_off;
+    unsigned long long* queue;
     Common C;
 };
 
@@ -1533,7 +1538,15 @@ template <int BS, bool MIXED, int WK>
 __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_list_kernel(ListParams P)
 {
     __shared__ double red[BS / 64];
-    for (int64_t p = blockIdx.x; p < P.total; p += gridDim.x) {
+    using T = std::conditional_t<MIXED, float, double>;
+    auto draw = [&]() -> int64_t {
+        if (threadIdx.x == 0) *(int64_t*)red = (int64_t)atomicAdd(P.queue, 1ull);
+        __syncthreads();
+        const int64_t v = *(const int64_t*)red;
+        __syncthreads();
+        return v;
+    };
+    for (int64_t p = draw(); p < P.total; p = draw()) {
         int lo = 0, hi = P.n_items - 1;  // last item with base <= p
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -1545,7 +1558,7 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_list_kernel(ListPara
         const int64_t ne = int64_t(2) << (2 * l);
         Job J;
         J.l = l;
-        J.kap = MIXED ? (const void*)((const float*)it.kappa + q * ne) : (const void*)((const double*)it.kappa + q * ne);
+        J.kap = (const T*)it.kappa + q * ne;
         J.G = it.G + q * P.C.nobs;
         J.p_out = nullptr;
         J.status = it.status ? it.status + q : nullptr;
@@ -1554,27 +1567,56 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_list_kernel(ListPara
         J.phi = it.phi ? it.phi + q : nullptr;
         J.obs_idx = P.obs_idx[l];
         J.obs_w = P.obs_w[l];
-        if (MIXED) {
-            float* ring = (WK == 2 && P.ring_off >= 0) ? (float*)mls_lds + P.ring_off : nullptr;
-            solve_one_mixed<BS, WK>(make_map((float*)P.ws + (int64_t)blockIdx.x * P.slot_elems, (float*)mls_lds, l,
-                                         P.lds_elems, nullptr, ring), J, P.C, red);
+        T* slot = (T*)P.ws + (int64_t)blockIdx.x * P.slot_elems;
+        T* ring = WK == 2 ? (T*)mls_lds + P.ring_off : nullptr;
+        if constexpr (MIXED) {
+            solve_one_mixed<BS, WK>(make_map(slot, (T*)mls_lds, l, P.lds_elems, nullptr, ring), J, P.C, red);
         } else {
-            double* slot = (double*)P.ws + (int64_t)blockIdx.x * P.slot_elems;
             double* cinv = P.cinv_lds ? (double*)mls_lds + P.lds_elems : slot + hier_elems(l, false);
-            double* ring = (WK == 2 && P.ring_off >= 0) ? (double*)mls_lds + P.ring_off : nullptr;
-            solve_one_f64<BS, WK, false>(make_map(slot, (double*)mls_lds, l, P.lds_elems, cinv, ring), J, P.C,
+            solve_one_f64<BS, WK, false>(make_map(slot, (T*)mls_lds, l, P.lds_elems, cinv, ring), J, P.C,
                                          red);  // work items carry no p_out
+        }
+    }
+    // as in solve_kernel: the last workgroup to finish resets the counter
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(P.queue + 1, 1ull) == (unsigned long long)(gridDim.x - 1)) {
+            atomicExch(P.queue, 0ull);
+            atomicExch(P.queue + 1, 0ull);
         }
     }
 }
 
 // ------------------------------------------------------------ launch --
+// From h = 1/128 on one workgroup of 1024 threads per CU: the particle's
+// passes stream from memory, and sixteen waves on one particle keep more
+// loads in flight than two particles' eight, over half the slots' footprint
+// (us per 512 solves, 512 threads at four workgroups per CU -> 1024 at one:
+// FP64 h = 1/128 6627 -> 5427, 1/256 26640 -> 20344, 1/512 101173 -> 78620;
+// mixed 4090 -> 3723, 17288 -> 17049, 77095 -> 74386; 64 solves at h = 1/512
+// 42.8 -> 30.6 ms).
 static int default_block(int l)
 {
     if (l <= 4) return 64;
     if (l == 5) return 128;
     if (l == 6) return 256;
-    return 512;
+    return 1024;
+}
+
+// LDS budget of level l in bytes.  The library's own choice beside the
+// default block: FP64 at h = 1/128 takes all there is (the fine level's FP32
+// weights of the V-cycle then fit: 5.43 ms per 512 solves against 5.78 at
+// 64 KiB), the mixed form none from h = 1/128 on (3.72 ms against 4.07; the
+// coarse levels' flat accesses cost more than L2 hits), else 64 KiB.
+static int64_t lds_budget(const mls2mc_ctx* ctx, int l, bool mixed)
+{
+    int64_t budget = ctx->solver_lds[l];
+    if (budget < 0) return 0;
+    if (budget == 0) {
+        const bool own = ctx->solver_block[l] == 0 && l >= 7;
+        budget = own && mixed ? 0 : own && l == 7 ? ctx->max_lds : 65536;
+    }
+    return budget < ctx->max_lds ? budget : ctx->max_lds;
 }
 
 static Common make_common(const mls2mc_ctx* ctx, int l)
@@ -1623,8 +1665,7 @@ static size_t lds_bytes_for(const mls2mc_ctx* ctx, int l, bool mixed, int bs, bo
                             int* cinv_lds, int64_t* ring_off)
 {
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
-    int64_t budget = ctx->solver_lds[l] >= 0 ? (ctx->solver_lds[l] ? ctx->solver_lds[l] : 65536) : 0;
-    if (budget > ctx->max_lds) budget = ctx->max_lds;
+    int64_t budget = lds_budget(ctx, l, mixed);
     // the row walks' rows come first: the residency gets what is left
     const int64_t ring = walks ? walk_ring_elems(bs, l) : 0;
     const int64_t ring_bytes = ring * (int64_t)esz;
@@ -1658,7 +1699,8 @@ int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
     slot = (slot + 63) & ~int64_t(63);  // 256/512-byte aligned slots
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
     int bs = ctx->solver_block[l] ? ctx->solver_block[l] : default_block(l);
-    int64_t grid = ctx->solver_grid[l] ? ctx->solver_grid[l] : (int64_t)dev_cus * (l <= 6 ? 8 : 4);
+    int64_t grid = ctx->solver_grid[l] ? ctx->solver_grid[l]
+                                       : (int64_t)dev_cus * (l <= 6 ? 8 : ctx->solver_block[l] ? 4 : 1);
     // cap the slot workspace at 16 GiB
     const int64_t cap = (int64_t)((16ull << 30) / (slot * esz));
     if (grid > cap) grid = cap;
@@ -1712,9 +1754,13 @@ int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
 // level first); lmax: finest level in the list; total: sum of N.
 static void list_shape(const mls2mc_ctx* ctx, int lmax, int64_t total, bool mixed, int64_t* grid,
                        int64_t* slot, int* bs);
+static int list_block(const mls2mc_ctx* ctx, int lmax)
+{
+    return ctx->list_block ? ctx->list_block : default_block(lmax);
+}
 
 int launch_solve_list(mls2mc_ctx* ctx, const SolveItem* items_dev, int n_items, int64_t total, int lmax,
-                      bool mixed, hipStream_t s)
+                      bool walked, bool mixed, hipStream_t s)
 {
     if (total == 0 || n_items == 0) return MLS2MC_OK;
     int64_t grid, slot;
@@ -1732,13 +1778,17 @@ int launch_solve_list(mls2mc_ctx* ctx, const SolveItem* items_dev, int n_items, 
         P.obs_idx[l] = ctx->obs[l].idx;
         P.obs_w[l] = ctx->obs[l].w;
     }
+    P.queue = ctx->d_queue;
     P.C = make_common(ctx, lmax);
-    // the work list mixes levels, so it keeps the separate V-cycle passes
-    const size_t lds = lds_bytes_for(ctx, lmax, mixed, bs, false, &P.lds_elems, &P.cinv_lds, &P.ring_off);
+    const bool fused = walked;
+    const size_t lds = lds_bytes_for(ctx, lmax, mixed, bs, fused, &P.lds_elems, &P.cinv_lds, &P.ring_off);
     dim3 g((unsigned)grid);
     // items of h = 1/64 and finer walk columns in the CG stencil pass (the
     // instance decides per item)
-    if (lmax >= 6) {
+    if (fused) {
+        if (mixed) { MLS_SWITCH_LIST(bs, true, 2, g, lds, s, P) }
+        else { MLS_SWITCH_LIST(bs, false, 2, g, lds, s, P) }
+    } else if (lmax >= 6) {
         if (mixed) { MLS_SWITCH_LIST(bs, true, 1, g, lds, s, P) }
         else { MLS_SWITCH_LIST(bs, false, 1, g, lds, s, P) }
     } else {
@@ -1808,14 +1858,14 @@ static void list_shape(const mls2mc_ctx* ctx, int lmax, int64_t total, bool mixe
     int64_t sl = solver_slot_elems(lmax, mixed);
     sl = (sl + 63) & ~int64_t(63);
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
-    int64_t g = ctx->list_grid ? ctx->list_grid : (int64_t)ctx->n_cu * 4;
+    int64_t g = ctx->list_grid ? ctx->list_grid : (int64_t)ctx->n_cu * (lmax >= 7 && !ctx->list_block ? 1 : 4);
     const int64_t cap = (int64_t)((16ull << 30) / (sl * esz));
     if (g > cap) g = cap;
     if (g > total) g = total;
     if (g < 1) g = 1;
     *grid = g;
     *slot = sl;
-    *bs = ctx->list_block ? ctx->list_block : default_block(lmax);
+    *bs = list_block(ctx, lmax);
 }
 
 int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vector<ListChunk>& out,
@@ -1884,10 +1934,18 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
         SolveItem* hs = (SolveItem*)(hb + off + ch.size() * sizeof(GemmItem));
         ListChunk lc;
         lc.n = (int)ch.size();
-        lc.n_list = 0;
         lc.tiles = 0;
-        lc.total = 0;
-        lc.lmax = 0;
+        // Particles of h = 1/256 and finer that fill the device get a launch
+        // of their own, with the fused row walks; fewer share the next launch
+        // with the smaller levels' particles, which fill the other CUs.
+        int64_t big = 0;
+        bool walks = true;
+        for (const Piece& pc : ch)
+            if (pc.it.l >= 8) {
+                big += pc.it.N;
+                walks = walks && launch_walks(pc.it.l, list_block(ctx, pc.it.l), make_common(ctx, pc.it.l).nu);
+            }
+        const bool split = walks && big >= ctx->n_cu;
         size_t kap_off = 0;
         for (size_t i = 0; i < ch.size(); ++i) {
             const FwdItem& it = ch[i].it;
@@ -1922,10 +1980,11 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
                 lv.total += it.N;
                 ++lv.n;
             } else {
-                v.base = lc.total;
-                lc.total += it.N;
-                ++lc.n_list;
-                lc.lmax = std::max(lc.lmax, it.l);
+                ListGroup& gr = lc.group[split && it.l >= 8 ? 0 : 1];
+                v.base = gr.total;
+                gr.total += it.N;
+                if (gr.n++ == 0) gr.first = (int)i;
+                gr.lmax = std::max(gr.lmax, it.l);
             }
             hs[i] = v;
         }
@@ -1933,10 +1992,11 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
         MLS_CHECK_HIP(hipMemcpyAsync(db + off, hb + off, bytes, hipMemcpyHostToDevice, s));
         lc.gemm = (const GemmItem*)(db + off);
         lc.solve = (const SolveItem*)(db + off + ch.size() * sizeof(GemmItem));
-        if (lc.total > 0) {
+        for (const ListGroup& gr : lc.group) {
+            if (gr.total == 0) continue;
             int64_t grid, slot;
             int bs;
-            list_shape(ctx, lc.lmax, lc.total, mixed, &grid, &slot, &bs);
+            list_shape(ctx, gr.lmax, gr.total, mixed, &grid, &slot, &bs);
             ws_need = std::max(ws_need, (size_t)grid * slot * esz);
         }
         out.push_back(lc);
@@ -1952,7 +2012,9 @@ int enqueue_list(mls2mc_ctx* ctx, const std::vector<ListChunk>& chunks, hipStrea
     const bool mixed = ctx->prob.precision == MLS2MC_MIXED;
     for (const auto& lc : chunks) {
         MLS_TRY(launch_kl_list(ctx, lc.gemm, lc.n, lc.tiles, s));
-        MLS_TRY(launch_solve_list(ctx, lc.solve, lc.n_list, lc.total, lc.lmax, mixed, s));
+        for (int g = 0; g < 2; ++g)
+            MLS_TRY(launch_solve_list(ctx, lc.solve + lc.group[g].first, lc.group[g].n, lc.group[g].total,
+                                      lc.group[g].lmax, g == 0, mixed, s));
         for (const ListLevel& lv : lc.levels)
             MLS_TRY(launch_resident_list(ctx, lv.l, lc.solve + lv.first, lv.n, lv.total, mixed, s));
     }
