@@ -127,18 +127,28 @@ __global__ __launch_bounds__(1024) void loss_delta_kernel(int64_t n, const float
     if (threadIdx.x == 0) loss[0] = (float)(s * scale);
 }
 
+// One Adam update; the contractions are spelled out so that every kernel
+// rounds alike.
+__device__ __forceinline__ float adam_update(float* __restrict__ p, float* __restrict__ m, float* __restrict__ v,
+                                             int64_t i, float gi, float lr, float b1, float b2, float c1, float c2,
+                                             float eps)
+{
+    const float mi = fmaf(1.f - b1, gi, b1 * m[i]);
+    const float vi = fmaf(gi, (1.f - b2) * gi, b2 * v[i]);
+    m[i] = mi;
+    v[i] = vi;
+    const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    p[i] = pi;
+    return pi;
+}
+
 __global__ void adam_kernel(int64_t n, float* __restrict__ p, const float* __restrict__ g,
                             float* __restrict__ m, float* __restrict__ v, float lr, float b1, float b2,
                             float c1, float c2, float eps)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    (void)adam_update(p, m, v, i, g[i], lr, b1, b2, c1, c2, eps);
 }
 
 // rows idx[b] (or b) of a double matrix, standardised, to float
@@ -214,6 +224,13 @@ struct Surrogate {
     float *X = nullptr, *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *OUT = nullptr;
     float *T = nullptr, *D3 = nullptr, *D2 = nullptr, *D1 = nullptr, *loss = nullptr;
     int32_t* perm = nullptr;
+    // fused path: BF16 copies of the weights as MFMA operands, and the
+    // transposed batch for the weight gradients (see MlpDims)
+    __bf16* w16 = nullptr;
+    bool w16_fresh = false;  // the copies are those of p
+    char* tr = nullptr;
+    int64_t tr_rows = 0;
+    double* lossp = nullptr;
     float* W1() const { return p; }
     float* b1() const { return p + (int64_t)H * D; }
     float* W2() const { return b1() + H; }
@@ -225,7 +242,8 @@ struct Surrogate {
 static void sur_free(Surrogate* S)
 {
     void* ptrs[] = {S->p, S->g, S->m, S->v, S->mu_x, S->sd_x, S->mu_y, S->sd_y, S->ds_th, S->ds_G,
-                    S->X, S->Z1, S->H1, S->Z2, S->H2, S->OUT, S->T, S->D3, S->D2, S->D1, S->loss, S->perm};
+                    S->X, S->Z1, S->H1, S->Z2, S->H2, S->OUT, S->T, S->D3, S->D2, S->D1, S->loss, S->perm,
+                    S->w16, S->tr, S->lossp};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     *S = Surrogate();
@@ -279,6 +297,426 @@ static int sur_backward(Surrogate* S, int64_t B, hipStream_t s)
     MLS_TRY((gemm<false, false, EPI_DGELU>((int)B, H, H, S->D2, H, S->W2(), H, nullptr, S->D1, nullptr, S->Z1, H, s)));
     // layer 1
     MLS_TRY((gemm<true, false, EPI_STORE_ASUM>(H, D, (int)B, S->D1, H, S->X, D, nullptr, gW1, gb1, nullptr, D, s)));
+    MLS_CHECK_HIP(hipGetLastError());
+    return MLS2MC_OK;
+}
+
+// ------------------------------------------------------ fused passes --
+// A training step on 256 rows is 0.16 GFLOP, microseconds of the matrix
+// cores; as twelve launches, each a chain of strided scalar loads, it took
+// 172 us (100 -> 256 -> 256 -> 49).  Now 34: everything before the weight
+// gradients is row-local, so one kernel (24 us; a chain of five layers'
+// load latencies in 16 workgroups bounds it; with 512 threads 27 us) takes 16
+// rows through standardisation, the three layers, the loss and the two
+// backward products with the activations in LDS, and a second one (9 us)
+// forms all weight gradients and applies Adam in their epilogue.
+// Weights are read as BF16 copies (kept by the Adam epilogue; rounding the
+// FP32 master as the fragments were loaded before gives the same operands)
+// and the batch is handed over transposed, so every fragment is one or two
+// 16-byte loads.  The MFMA tiles, their k order and the FP32 epilogues are
+// those of mlp_gemm, so the parameters are bitwise the same.
+struct MlpDims {
+    int D, H, O;     // inputs, hidden width (a multiple of 16), outputs
+    int Dp, Hp, Op;  // as k extents: padded to 32
+    int Or;          // outputs as rows: padded to 16
+    // element offsets of the BF16 copies: rows x padded k
+    int64_t w1() const { return 0; }                         // H x Dp
+    int64_t w2() const { return (int64_t)H * Dp; }           // H x Hp
+    int64_t w3() const { return w2() + (int64_t)H * Hp; }    // Or x Hp
+    int64_t w2t() const { return w3() + (int64_t)Or * Hp; }  // H x Hp
+    int64_t w3t() const { return w2t() + (int64_t)H * Hp; }  // H x Op
+    int64_t total() const { return w3t() + (int64_t)H * Op; }
+    // bytes of LDS of the row kernel: X, H1, H2 (later D2), D3 in BF16 rows
+    // padded against bank conflicts, Z1 and Z2 in FP32, the loss partials
+    size_t lds() const
+    {
+        return 2 * 16 * (size_t)(Dp + 8 + 2 * (Hp + 8) + Op + 8) + 2 * 4 * 16 * (size_t)H + 64;
+    }
+};
+static MlpDims mlp_dims(const Surrogate* S)
+{
+    auto up = [](int x, int m) { return (x + m - 1) / m * m; };
+    return {S->D, S->H, S->O, up(S->D, 32), up(S->H, 32), up(S->O, 32), up(S->O, 16)};
+}
+
+struct MlpRows {
+    int D, H, O, Dp, Hp, Op, Or;
+    const __bf16 *w1, *w2, *w3, *w2t, *w3t;
+    const float *b1, *b2, *b3;
+    int64_t B, Bp;           // rows, and padded to 32 (the batch's k extent)
+    const int32_t* idx;      // rows of th and G (null: 0 .. B - 1)
+    const double *th, *G;    // inputs, targets (G: outputs in a prediction)
+    const float *mux, *sdx, *muy, *sdy;  // standardisation, or null
+    double* out;             // prediction: B x O
+    float scale;
+    __bf16 *xt, *h1t, *h2t;  // training: features x Bp
+    float *d3t, *d2t, *d1t;
+    double* lossp;           // per workgroup
+};
+
+// C[16 x 16 tile n0] = A (LDS, 16 rows of lda) x W^T (rows n0 .. n0+15 of Kp)
+__device__ __forceinline__ flt4 row_tile(const __bf16* a, int lda, const __bf16* __restrict__ w, int Kp, int n0)
+{
+    const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
+    const bf16x8* ap = reinterpret_cast<const bf16x8*>(a + r * lda + 8 * kq);
+    const bf16x8* wp = reinterpret_cast<const bf16x8*>(w + (int64_t)(n0 + r) * Kp + 8 * kq);
+    flt4 acc = {0.f, 0.f, 0.f, 0.f};
+    int k = 0;
+    for (; k + 8 <= Kp / 32; k += 8) {  // a round of loads in flight, then its MFMAs
+        bf16x8 wf[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) wf[u] = wp[4 * (k + u)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[4 * (k + u)], wf[u], acc, 0, 0, 0);
+    }
+    for (; k + 2 <= Kp / 32; k += 2) {
+        const bf16x8 w0 = wp[4 * k], w1 = wp[4 * k + 4];
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[4 * k], w0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[4 * k + 4], w1, acc, 0, 0, 0);
+    }
+    for (; k < Kp / 32; ++k) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[4 * k], wp[4 * k], acc, 0, 0, 0);
+    return acc;
+}
+
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store4(float* p, const float (&v)[4])
+{
+    *reinterpret_cast<flt4*>(p) = flt4{v[0], v[1], v[2], v[3]};
+}
+__device__ __forceinline__ void store4(__bf16* p, const float (&v)[4])
+{
+    *reinterpret_cast<bf16x4*>(p) = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
+}
+
+extern __shared__ __align__(16) char mlp_lds[];
+
+constexpr int kRowThreads = 1024;
+template <bool TRAIN>
+__global__ __launch_bounds__(kRowThreads) void mlp_rows_kernel(MlpRows P)
+{
+    __shared__ double red[kRowThreads / 64];
+    const int ldx = P.Dp + 8, ldh = P.Hp + 8, ldo = P.Op + 8;
+    __bf16* X = reinterpret_cast<__bf16*>(mlp_lds);
+    __bf16* H1 = X + 16 * ldx;
+    __bf16* H2 = H1 + 16 * ldh;  // D2 in the backward products
+    __bf16* D3 = H2 + 16 * ldh;
+    float* Z1 = reinterpret_cast<float*>(D3 + 16 * ldo);
+    float* Z2 = Z1 + 16 * P.H;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r = lane & 15, kq = lane >> 4;
+    constexpr int NW = kRowThreads / 64;
+    const int64_t b0 = blockIdx.x * (int64_t)16;
+    // standardised inputs; the padded k columns and rows past the batch are zero
+    for (int q = tid; q < 16 * P.Dp; q += kRowThreads) {
+        const int row = q / P.Dp, k = q - row * P.Dp;
+        float x = 0.f;
+        if (b0 + row < P.B && k < P.D) {
+            const int64_t src = P.idx ? P.idx[b0 + row] : b0 + row;
+            const double v = P.th[src * P.D + k];
+            x = P.mux ? (float)((v - (double)P.mux[k]) / (double)P.sdx[k]) : (float)v;
+        }
+        X[row * ldx + k] = (__bf16)x;
+    }
+    for (int q = tid; q < 16 * (P.Hp - P.H); q += kRowThreads) {
+        const int row = q / (P.Hp - P.H), k = P.H + q % (P.Hp - P.H);
+        H1[row * ldh + k] = H2[row * ldh + k] = (__bf16)0.f;
+    }
+    if (TRAIN)
+        for (int q = tid; q < 16 * P.Op; q += kRowThreads) D3[(q / P.Op) * ldo + q % P.Op] = (__bf16)0.f;
+    __syncthreads();
+    if (TRAIN)
+        for (int q = tid; q < 2 * P.D; q += kRowThreads) {  // X transposed, eight rows per store
+            const int k = q >> 1, row = 8 * (q & 1);
+            bf16x8 v;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = X[(row + u) * ldx + k];
+            *reinterpret_cast<bf16x8*>(P.xt + k * P.Bp + b0 + row) = v;
+        }
+    auto hidden = [&](const __bf16* a, int lda, const __bf16* w, int Kp, const float* b, float* Z, __bf16* Hout,
+                      __bf16* ht) {
+        for (int n0 = 16 * wv; n0 < P.H; n0 += 16 * NW) {
+            const flt4 acc = row_tile(a, lda, w, Kp, n0);
+            const int n = n0 + r;
+            float h[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float z = acc[v];
+                z += b[n];
+                h[v] = gelu(z);
+                if (TRAIN) Z[(4 * kq + v) * P.H + n] = z;
+                Hout[(4 * kq + v) * ldh + n] = (__bf16)h[v];
+            }
+            if (TRAIN) store4(ht + n * P.Bp + b0 + 4 * kq, h);
+        }
+        __syncthreads();
+    };
+    hidden(X, ldx, P.w1, P.Dp, P.b1, Z1, H1, P.h1t);
+    hidden(H1, ldh, P.w2, P.Hp, P.b2, Z2, H2, P.h2t);
+    double loss = 0.0;
+    for (int n0 = 16 * wv; n0 < P.Or; n0 += 16 * NW) {
+        const flt4 acc = row_tile(H2, ldh, P.w3, P.Hp, n0);
+        const int n = n0 + r;
+        if (n >= P.O) continue;
+        float d3[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t row = b0 + 4 * kq + v;
+            const float o = acc[v] + P.b3[n];
+            d3[v] = 0.f;
+            if (row < P.B) {
+                if (TRAIN) {
+                    const int64_t src = P.idx ? P.idx[row] : row;
+                    const double g = P.G[src * P.O + n];
+                    const float t = P.muy ? (float)((g - (double)P.muy[n]) / (double)P.sdy[n]) : (float)g;
+                    const float d = o - t;
+                    d3[v] = d * P.scale;
+                    loss += 0.5 * (double)d * (double)d;
+                } else {
+                    P.out[row * P.O + n] = P.muy ? (double)P.muy[n] + (double)P.sdy[n] * (double)o : (double)o;
+                }
+            }
+            if (TRAIN) D3[(4 * kq + v) * ldo + n] = (__bf16)d3[v];
+        }
+        if (TRAIN) store4(P.d3t + n * P.Bp + b0 + 4 * kq, d3);
+    }
+    if (!TRAIN) return;
+    loss = block_sum<kRowThreads>(loss, red);  // its barriers end the layer
+    if (tid == 0) P.lossp[blockIdx.x] = loss;
+    auto backward = [&](const __bf16* a, int lda, const __bf16* w, int Kp, const float* Z, __bf16* Dout, float* dt) {
+        for (int n0 = 16 * wv; n0 < P.H; n0 += 16 * NW) {
+            const flt4 acc = row_tile(a, lda, w, Kp, n0);
+            const int n = n0 + r;
+            float d[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                d[v] = acc[v] * gelu_d(Z[(4 * kq + v) * P.H + n]);
+                if (Dout) Dout[(4 * kq + v) * ldh + n] = (__bf16)d[v];
+            }
+            store4(dt + n * P.Bp + b0 + 4 * kq, d);
+        }
+    };
+    backward(D3, ldo, P.w3t, P.Op, Z2, H2, P.d2t);
+    __syncthreads();
+    backward(H2, ldh, P.w2t, P.Hp, Z1, nullptr, P.d1t);
+}
+
+// Weight gradients dW = D^T H of the three layers and the bias gradients
+// (row sums of D^T), one 16 x 16 tile per wave, with the Adam update and the
+// refreshed BF16 copies in the epilogue (ADAM), or stored to g.
+struct MlpGrad {
+    int M[3], N[3];                       // outs x ins per layer
+    int tiles[3], tn[3];                  // 16 x 16 tiles, tiles per row
+    const float* dt[3];                   // M x Bp
+    const __bf16* ht[3];                  // N x Bp
+    int64_t w[3], b[3];                   // parameter offsets
+    __bf16* c[3];                         // BF16 copy, M x ldc
+    __bf16* ct[3];                        // transposed copy, N x ldt (or null)
+    int ldc[3], ldt[3];
+    int64_t Bp;
+    float *p, *m, *v, *g;
+    float lr, b1, b2, c1, c2, eps;
+};
+
+template <bool ADAM>
+__global__ __launch_bounds__(256) void mlp_grad_kernel(MlpGrad P)
+{
+    int t = blockIdx.x * 4 + (threadIdx.x >> 6), l = 0;
+    while (l < 3 && t >= P.tiles[l]) t -= P.tiles[l++];
+    if (l == 3) return;
+    const int lane = threadIdx.x & 63, r = lane & 15, kq = lane >> 4;
+    const int M = P.M[l], N = P.N[l];
+    const int m0 = 16 * (t / P.tn[l]), n0 = 16 * (t % P.tn[l]);
+    const int am = m0 + r, bn = n0 + r;
+    // rows past the layer's sizes repeat the last one; their products are not stored
+    const float* dp = P.dt[l] + (int64_t)(am < M ? am : M - 1) * P.Bp + 8 * kq;
+    const __bf16* hp = P.ht[l] + (int64_t)(bn < N ? bn : N - 1) * P.Bp + 8 * kq;
+    flt4 acc = {0.f, 0.f, 0.f, 0.f};
+    float rs = 0.f;
+    for (int64_t k0 = 0; k0 < P.Bp; k0 += 128) {
+        flt4 a0[4], a1[4];
+        bf16x8 b[4];
+        const int nu = P.Bp - k0 < 128 ? (int)(P.Bp - k0) / 32 : 4;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (u < nu) {
+                a0[u] = *reinterpret_cast<const flt4*>(dp + k0 + 32 * u);
+                a1[u] = *reinterpret_cast<const flt4*>(dp + k0 + 32 * u + 4);
+                b[u] = *reinterpret_cast<const bf16x8*>(hp + k0 + 32 * u);
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (u < nu) {
+                bf16x8 a;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    a[q] = (__bf16)a0[u][q];
+                    a[4 + q] = (__bf16)a1[u][q];
+                }
+                if (n0 == 0) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) rs += a0[u][q];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) rs += a1[u][q];
+                }
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[u], acc, 0, 0, 0);
+            }
+    }
+    auto step = [&](int64_t i, float gi) {
+        return adam_update(P.p, P.m, P.v, i, gi, P.lr, P.b1, P.b2, P.c1, P.c2, P.eps);
+    };
+    if (n0 == 0) {
+        rs += __shfl_xor(rs, 16);
+        rs += __shfl_xor(rs, 32);
+        if (kq == 0 && am < M) {
+            if (ADAM) (void)step(P.b[l] + am, rs);
+            else P.g[P.b[l] + am] = rs;
+        }
+    }
+    const int n = n0 + r;
+    if (n >= N) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int m = m0 + 4 * kq + v;
+        if (m >= M) continue;
+        const int64_t i = P.w[l] + (int64_t)m * N + n;
+        if (ADAM) {
+            const __bf16 w = (__bf16)step(i, acc[v]);
+            P.c[l][(int64_t)m * P.ldc[l] + n] = w;
+            if (P.ct[l]) P.ct[l][(int64_t)n * P.ldt[l] + m] = w;
+        } else {
+            P.g[i] = acc[v];
+        }
+    }
+}
+
+// the BF16 copies of a layer's M x N weights
+__global__ void mlp_copy_kernel(int M, int N, const float* __restrict__ w, __bf16* __restrict__ c, int ldc,
+                                __bf16* __restrict__ ct, int ldt)
+{
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i >= (int64_t)M * N) return;
+    const int m = (int)(i / N), n = (int)(i - (int64_t)m * N);
+    const __bf16 v = (__bf16)w[i];
+    c[(int64_t)m * ldc + n] = v;
+    if (ct) ct[(int64_t)n * ldt + m] = v;
+}
+
+__global__ void zero16_kernel(int64_t n, __bf16* __restrict__ p)
+{
+    const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+    if (i < n) p[i] = (__bf16)0.f;
+}
+
+__global__ __launch_bounds__(256) void loss_sum_kernel(int n, const double* __restrict__ part, float scale,
+                                                       float* __restrict__ loss)
+{
+    __shared__ double red[4];
+    double s = 0.0;
+    for (int k = threadIdx.x; k < n; k += 256) s += part[k];
+    s = block_sum<256>(s, red);
+    if (threadIdx.x == 0) loss[0] = (float)(s * scale);
+}
+
+// The row kernel's LDS must fit beside its static array; wider networks keep
+// the layer-by-layer products.
+static bool mlp_fits(const mls2mc_ctx* ctx) { return mlp_dims(ctx->sur).lds() <= (size_t)ctx->max_lds; }
+
+// the BF16 copies, made anew when the parameters changed outside training
+static int mlp_refresh(Surrogate* S, hipStream_t s)
+{
+    const MlpDims d = mlp_dims(S);
+    if (!S->w16) {
+        MLS_CHECK_HIP(hipMalloc(&S->w16, sizeof(__bf16) * (size_t)d.total()));
+        zero16_kernel<<<(unsigned)((d.total() + 255) / 256), 256, 0, s>>>(d.total(), S->w16);
+        S->w16_fresh = false;
+    }
+    if (S->w16_fresh) return MLS2MC_OK;
+    auto copy = [&](int M, int N, const float* w, int64_t c, int ldc, int64_t ct, int ldt) {
+        mlp_copy_kernel<<<(unsigned)(((int64_t)M * N + 255) / 256), 256, 0, s>>>(M, N, w, S->w16 + c, ldc,
+                                                                                ct >= 0 ? S->w16 + ct : nullptr, ldt);
+    };
+    copy(d.H, d.D, S->W1(), d.w1(), d.Dp, -1, 0);
+    copy(d.H, d.H, S->W2(), d.w2(), d.Hp, d.w2t(), d.Hp);
+    copy(d.O, d.H, S->W3(), d.w3(), d.Hp, d.w3t(), d.Op);
+    MLS_CHECK_HIP(hipGetLastError());
+    S->w16_fresh = true;
+    return MLS2MC_OK;
+}
+
+static MlpRows mlp_rows(const Surrogate* S, int64_t B)
+{
+    const MlpDims d = mlp_dims(S);
+    MlpRows P = {};
+    P.D = d.D; P.H = d.H; P.O = d.O; P.Dp = d.Dp; P.Hp = d.Hp; P.Op = d.Op; P.Or = d.Or;
+    P.w1 = S->w16 + d.w1(); P.w2 = S->w16 + d.w2(); P.w3 = S->w16 + d.w3();
+    P.w2t = S->w16 + d.w2t(); P.w3t = S->w16 + d.w3t();
+    P.b1 = S->b1(); P.b2 = S->b2(); P.b3 = S->b3();
+    P.B = B;
+    P.Bp = (B + 31) / 32 * 32;
+    return P;
+}
+
+// loss and gradient of B rows of the training arrays: into the parameters
+// (an Adam step) or into S->g
+static int mlp_step(Surrogate* S, int64_t B, const int32_t* idx, const double* th, const double* G, bool standardise,
+                    bool adam, float lr, float b1, float b2, float c1, float c2, float eps, hipStream_t s)
+{
+    const MlpDims d = mlp_dims(S);
+    MlpRows P = mlp_rows(S, B);
+    if (S->tr_rows < P.Bp) {
+        if (S->tr) MLS_CHECK_HIP(hipFree(S->tr));
+        if (S->lossp) MLS_CHECK_HIP(hipFree(S->lossp));
+        S->tr = nullptr;
+        S->lossp = nullptr;
+        S->tr_rows = 0;
+        MLS_CHECK_HIP(hipMalloc(&S->tr, (size_t)P.Bp * (4 * (2 * d.H + d.O) + 2 * (2 * d.H + d.D))));
+        MLS_CHECK_HIP(hipMalloc(&S->lossp, sizeof(double) * (size_t)(P.Bp / 16)));
+        S->tr_rows = P.Bp;
+    }
+    P.d3t = reinterpret_cast<float*>(S->tr);
+    P.d2t = P.d3t + d.O * P.Bp;
+    P.d1t = P.d2t + d.H * P.Bp;
+    P.h1t = reinterpret_cast<__bf16*>(P.d1t + d.H * P.Bp);
+    P.h2t = P.h1t + d.H * P.Bp;
+    P.xt = P.h2t + d.H * P.Bp;
+    P.lossp = S->lossp;
+    P.idx = idx; P.th = th; P.G = G;
+    if (standardise) { P.mux = S->mu_x; P.sdx = S->sd_x; P.muy = S->mu_y; P.sdy = S->sd_y; }
+    P.scale = 1.0f / (float)(B * d.O);
+    const unsigned wg = (unsigned)(P.Bp / 16);
+    mlp_rows_kernel<true><<<wg, kRowThreads, d.lds(), s>>>(P);
+    MLS_CHECK_HIP(hipGetLastError());
+    MlpGrad g = {};
+    const int Ms[3] = {d.H, d.H, d.O}, Ns[3] = {d.D, d.H, d.H};
+    const float* dts[3] = {P.d1t, P.d2t, P.d3t};
+    const __bf16* hts[3] = {P.xt, P.h1t, P.h2t};
+    const float *ws[3] = {S->W1(), S->W2(), S->W3()}, *bs[3] = {S->b1(), S->b2(), S->b3()};
+    __bf16* cs[3] = {S->w16 + d.w1(), S->w16 + d.w2(), S->w16 + d.w3()};
+    __bf16* cts[3] = {nullptr, S->w16 + d.w2t(), S->w16 + d.w3t()};
+    int tiles = 0;
+    for (int l = 0; l < 3; ++l) {
+        g.M[l] = Ms[l]; g.N[l] = Ns[l];
+        g.tn[l] = (Ns[l] + 15) / 16;
+        g.tiles[l] = g.tn[l] * ((Ms[l] + 15) / 16);
+        g.dt[l] = dts[l]; g.ht[l] = hts[l];
+        g.w[l] = ws[l] - S->p; g.b[l] = bs[l] - S->p;
+        g.c[l] = cs[l]; g.ct[l] = cts[l];
+        g.ldc[l] = l == 0 ? d.Dp : d.Hp;
+        g.ldt[l] = l == 1 ? d.Hp : d.Op;
+        tiles += g.tiles[l];
+    }
+    g.Bp = P.Bp;
+    g.p = S->p; g.m = S->m; g.v = S->v; g.g = S->g;
+    g.lr = lr; g.b1 = b1; g.b2 = b2; g.c1 = c1; g.c2 = c2; g.eps = eps;
+    if (adam) mlp_grad_kernel<true><<<(tiles + 3) / 4, 256, 0, s>>>(g);
+    else mlp_grad_kernel<false><<<(tiles + 3) / 4, 256, 0, s>>>(g);
+    MLS_CHECK_HIP(hipGetLastError());
+    return MLS2MC_OK;
+}
+
+// the loss of the last mlp_step on B rows into S->loss
+static int mlp_loss(Surrogate* S, int64_t B, hipStream_t s)
+{
+    loss_sum_kernel<<<1, 256, 0, s>>>((int)((B + 31) / 32 * 2), S->lossp, 1.0f / (float)(B * S->O), S->loss);
     MLS_CHECK_HIP(hipGetLastError());
     return MLS2MC_OK;
 }
@@ -476,6 +914,7 @@ int mls2mc_surrogate_n_params(const mls2mc_ctx* ctx)
 int mls2mc_surrogate_set_params(mls2mc_ctx* ctx, const float* params, void* stream)
 {
     MLS_REQUIRE(ctx && ctx->sur && params, "surrogate_set_params: no surrogate or null pointer");
+    ctx->sur->w16_fresh = false;
     MLS_CHECK_HIP(hipMemcpyAsync(ctx->sur->p, params, sizeof(float) * ctx->sur->np, hipMemcpyDeviceToDevice,
                                  (hipStream_t)stream));
     return MLS2MC_OK;
@@ -526,7 +965,9 @@ int mls2mc_surrogate_train(mls2mc_ctx* ctx, int epochs, int batch, double lr, ui
     MLS_REQUIRE(epochs >= 0 && batch >= 1 && batch <= 65536 && lr > 0, "surrogate_train: bad epochs/batch/lr");
     MLS_REQUIRE(S->count >= batch, "surrogate_train: fewer pairs than one batch");
     const hipStream_t s = (hipStream_t)stream;
-    MLS_TRY(sur_ensure_batch(S, batch));
+    const bool fused = mlp_fits(ctx);
+    if (fused) MLS_TRY(mlp_refresh(S, s));
+    else MLS_TRY(sur_ensure_batch(S, batch));
     const int64_t n = S->count;
     // standardisation statistics of the current dataset
     col_stats_kernel<<<S->D, 256, 0, s>>>(n, S->D, S->ds_th, S->mu_x, S->sd_x);
@@ -544,18 +985,24 @@ int mls2mc_surrogate_train(mls2mc_ctx* ctx, int epochs, int batch, double lr, ui
         double ep_loss = 0.0;
         for (int64_t bi = 0; bi < nb; ++bi) {
             const int32_t* idx = S->perm + bi * batch;
-            standardize_kernel<<<(unsigned)((batch * S->D + 255) / 256), 256, 0, s>>>(batch, S->D, idx, S->ds_th,
-                                                                                     S->mu_x, S->sd_x, S->X);
-            standardize_kernel<<<(unsigned)((batch * S->O + 255) / 256), 256, 0, s>>>(batch, S->O, idx, S->ds_G,
-                                                                                     S->mu_y, S->sd_y, S->T);
-            MLS_CHECK_HIP(hipGetLastError());
-            MLS_TRY(sur_forward(S, batch, s));
-            MLS_TRY(sur_backward(S, batch, s));
             ++S->adam_t;
             const float c1 = 1.f - std::pow(b1, (float)S->adam_t), c2 = 1.f - std::pow(b2, (float)S->adam_t);
-            adam_kernel<<<(unsigned)((S->np + 255) / 256), 256, 0, s>>>(S->np, S->p, S->g, S->m, S->v, (float)lr,
-                                                                        b1, b2, c1, c2, eps);
-            MLS_CHECK_HIP(hipGetLastError());
+            if (fused) {
+                MLS_TRY(mlp_step(S, batch, idx, S->ds_th, S->ds_G, true, true, (float)lr, b1, b2, c1, c2, eps, s));
+                if (bi == nb - 1 && loss_out) MLS_TRY(mlp_loss(S, batch, s));
+            } else {
+                standardize_kernel<<<(unsigned)((batch * S->D + 255) / 256), 256, 0, s>>>(batch, S->D, idx, S->ds_th,
+                                                                                         S->mu_x, S->sd_x, S->X);
+                standardize_kernel<<<(unsigned)((batch * S->O + 255) / 256), 256, 0, s>>>(batch, S->O, idx, S->ds_G,
+                                                                                         S->mu_y, S->sd_y, S->T);
+                MLS_CHECK_HIP(hipGetLastError());
+                MLS_TRY(sur_forward(S, batch, s));
+                MLS_TRY(sur_backward(S, batch, s));
+                adam_kernel<<<(unsigned)((S->np + 255) / 256), 256, 0, s>>>(S->np, S->p, S->g, S->m, S->v, (float)lr,
+                                                                            b1, b2, c1, c2, eps);
+                MLS_CHECK_HIP(hipGetLastError());
+                S->w16_fresh = false;
+            }
             if (bi == nb - 1 && loss_out) {
                 float l;
                 MLS_CHECK_HIP(hipMemcpyAsync(&l, S->loss, sizeof(float), hipMemcpyDeviceToHost, s));
@@ -578,6 +1025,17 @@ int mls2mc_surrogate_predict(mls2mc_ctx* ctx, int64_t N, const double* theta, do
         return launch_linear_map(N, ctx->prob.K, ctx->nobs, ctx->d_sur_S, theta, G_out, (hipStream_t)stream);
     Surrogate* S = ctx->sur;
     const hipStream_t s = (hipStream_t)stream;
+    if (mlp_fits(ctx)) {
+        MLS_REQUIRE((N + 15) / 16 < (int64_t(1) << 31), "surrogate_predict: N too large for one launch");
+        MLS_TRY(mlp_refresh(S, s));
+        MlpRows P = mlp_rows(S, N);
+        P.th = theta;
+        P.out = G_out;
+        if (S->standardized) { P.mux = S->mu_x; P.sdx = S->sd_x; P.muy = S->mu_y; P.sdy = S->sd_y; }
+        mlp_rows_kernel<false><<<(unsigned)((N + 15) / 16), kRowThreads, mlp_dims(S).lds(), s>>>(P);
+        MLS_CHECK_HIP(hipGetLastError());
+        return MLS2MC_OK;
+    }
     const int64_t chunk = 4096;
     MLS_TRY(sur_ensure_batch(S, std::min(N, chunk)));
     for (int64_t q0 = 0; q0 < N; q0 += chunk) {
@@ -606,12 +1064,18 @@ int mls2mc_surrogate_loss_grad(mls2mc_ctx* ctx, int64_t B, const double* x, cons
     MLS_REQUIRE(x && target && loss_out && grad_out, "surrogate_loss_grad: null pointer");
     Surrogate* S = ctx->sur;
     const hipStream_t s = (hipStream_t)stream;
-    MLS_TRY(sur_ensure_batch(S, B));
-    standardize_kernel<<<(unsigned)((B * S->D + 255) / 256), 256, 0, s>>>(B, S->D, nullptr, x, nullptr, nullptr, S->X);
-    standardize_kernel<<<(unsigned)((B * S->O + 255) / 256), 256, 0, s>>>(B, S->O, nullptr, target, nullptr, nullptr, S->T);
-    MLS_CHECK_HIP(hipGetLastError());
-    MLS_TRY(sur_forward(S, B, s));
-    MLS_TRY(sur_backward(S, B, s));
+    if (mlp_fits(ctx)) {
+        MLS_TRY(mlp_refresh(S, s));
+        MLS_TRY(mlp_step(S, B, nullptr, x, target, false, false, 0.f, 0.f, 0.f, 1.f, 1.f, 0.f, s));
+        MLS_TRY(mlp_loss(S, B, s));
+    } else {
+        MLS_TRY(sur_ensure_batch(S, B));
+        standardize_kernel<<<(unsigned)((B * S->D + 255) / 256), 256, 0, s>>>(B, S->D, nullptr, x, nullptr, nullptr, S->X);
+        standardize_kernel<<<(unsigned)((B * S->O + 255) / 256), 256, 0, s>>>(B, S->O, nullptr, target, nullptr, nullptr, S->T);
+        MLS_CHECK_HIP(hipGetLastError());
+        MLS_TRY(sur_forward(S, B, s));
+        MLS_TRY(sur_backward(S, B, s));
+    }
     MLS_CHECK_HIP(hipMemcpyAsync(grad_out, S->g, sizeof(float) * S->np, hipMemcpyDeviceToDevice, s));
     MLS_CHECK_HIP(hipMemcpyAsync(loss_out, S->loss, sizeof(float), hipMemcpyDeviceToDevice, s));
     return MLS2MC_OK;
