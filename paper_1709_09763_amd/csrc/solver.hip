@@ -527,9 +527,8 @@ __device__ double up_step(const Lv<T, W>& L, const Lv<T>& C, const T* __restrict
 // residual update's inputs, which the band below overwrites only at the end
 // of its walk; above j1 it recomputes the red and black values from the
 // updated residual, which the band above stored in its first steps.  The up
-// walk reads only values that no band writes during it (the down walk's z,
-// the right-hand side, the coarse correction) and writes the new z to a
-// second array, so its bands need no ordering at all.
+// walk reads only values that no band writes during it (the right-hand side,
+// the weights, the coarse correction), so its bands need no ordering at all.
 template <int BS>
 __device__ __forceinline__ bool walk_level(int n, int nu)
 {
@@ -537,11 +536,12 @@ __device__ __forceinline__ bool walk_level(int n, int nu)
 }
 
 // LDS elements of the walks on a level of width n: per band four rows of
-// the node values and four rows of the red residuals (one per thread)
+// the node values and four rows of red residuals (down) or of the down-leg's
+// red values (up), one per thread between two zeros
 __host__ __device__ inline int64_t walk_ring_elems_level(int bs, int n)
 {
     const int64_t m = bs / (n >> 1);
-    return m * (4 * (int64_t)(n + 1) + 4 * (int64_t)((n >> 1) + 1));
+    return m * (4 * (int64_t)(n + 1) + 4 * (int64_t)((n >> 1) + 2));
 }
 // the most any walked level of a hierarchy with finest level l needs
 __host__ __device__ inline int64_t walk_ring_elems(int bs, int l)
@@ -574,7 +574,7 @@ __device__ __forceinline__ WalkRows walk_rows(int n)
     const int rows = n / m;
     w.j0 = 1 + band * rows;
     w.j1 = min(n, w.j0 + rows);
-    w.ring_off = (int64_t)band * (4 * (n + 1) + 4 * (P + 1));
+    w.ring_off = (int64_t)band * (4 * (n + 1) + 4 * (P + 2));
     return w;
 }
 
@@ -608,17 +608,20 @@ __device__ __forceinline__ void lds_barrier()
 // node of row j, the black node of row j-1 and the red node of row j-2 all
 // sit in it.  The node values of the last four rows are kept in the LDS
 // ring (the thread's own ones too); the weights come from registers on the
-// finest level and from memory on a walked coarse level (see below).
+// finest level and from memory on a walked coarse level (see below).  z is
+// not stored: the up-leg overwrites its black values without reading them,
+// and forms its red ones, b / d, again (16 B less per unknown than storing
+// and reading z back).
 template <int BS, bool FINE, typename T, typename W>
 __device__ void walk_down(const Lv<T, W>& L, const Lv<T>& C, T* __restrict__ b, const T* __restrict__ Q, T alpha,
-                          T* __restrict__ x, T* __restrict__ X, const T* __restrict__ Pn, T* __restrict__ ring)
+                          T* __restrict__ X, const T* __restrict__ Pn, T* __restrict__ ring)
 {
     const int n = L.n, s = L.s, P = n >> 1, sc = C.s, nc = C.n;
     const WalkRows w = walk_rows<BS>(n);
     const int t = w.t, j0 = w.j0, j1 = w.j1, ca = 2 * t;
     const lmem<T> lring = (lmem<T>)ring;
     const lmem<T> zr = lring + w.ring_off;  // node values, 4 rows of s
-    const lmem<T> rr = zr + 4 * s;          // red residuals, 4 rows of P + 1
+    const lmem<T> rr = zr + 4 * s;          // red residuals, 4 rows of P + 2
     // columns 0 and n of the rows are never written: they read as the zero boundary
     for (int k = threadIdx.x; k < walk_ring_elems_level(BS, n); k += BS) lring[k] = T(0);
     __syncthreads();
@@ -626,7 +629,6 @@ __device__ void walk_down(const Lv<T, W>& L, const Lv<T>& C, T* __restrict__ b, 
     const gmem<const W> wy = (gmem<const W>)L.wy;
     const gmem<T> gb = (gmem<T>)b;
     const gmem<const T> gQ = (gmem<const T>)Q;
-    const gmem<T> gx = (gmem<T>)x;
     const gmem<T> gX = (gmem<T>)X;
     const gmem<const T> gPn = (gmem<const T>)Pn;
     const gmem<T> gCb = (gmem<T>)C.b;
@@ -710,10 +712,6 @@ __device__ void walk_down(const Lv<T, W>& L, const Lv<T>& C, T* __restrict__ b, 
                            + WY(j, 1, k) * Z(j, i);
                 Z(jb, i) = (r1[k] + nb) / (WX(j, 1, k) + WX(j, 1, k + 1) + WY(j, 2, k) + WY(j, 1, k));
             }
-            if (jb >= j0 && jb < j1) {  // row j-1 is final: store both columns (streaming)
-                if (ca > 0) __builtin_nontemporal_store((T)Z(jb, ca), &gx[jb * s + ca]);
-                __builtin_nontemporal_store((T)Z(jb, ca + 1), &gx[jb * s + ca + 1]);
-            }
         }
         // ---- row j-2: the red residual (black neighbours final)
         const int jc = j - 2;
@@ -722,15 +720,15 @@ __device__ void walk_down(const Lv<T, W>& L, const Lv<T>& C, T* __restrict__ b, 
             const T d = WX(j, 2, k) + WX(j, 2, k + 1) + WY(j, 3, k) + WY(j, 2, k);
             const T lnb = WX(j, 2, k) * Z(jc, i - 1) + WX(j, 2, k + 1) * Z(jc, i + 1) + WY(j, 3, k) * Z(jc - 1, i)
                         + WY(j, 2, k) * Z(jc + 1, i);
-            rr[(jc & 3) * (P + 1) + t] = r2[k] - (d * Z(jc, i) - lnb);
+            rr[(jc & 3) * (P + 2) + t] = r2[k] - (d * Z(jc, i) - lnb);
         }
         // ---- coarse row (j-4)/2: restriction of the red residuals
         if (k == 0) {
             const int J = (j - 4) >> 1;
             if (J >= 1 && J <= nc - 1 && 2 * J >= j0 && 2 * J < j1 && t >= 1 && t <= nc - 1) {
-                const T a0 = rr[((2 * J) & 3) * (P + 1) + t];
-                const T ap = rr[((2 * J + 1) & 3) * (P + 1) + t];
-                const T am = rr[((2 * J - 1) & 3) * (P + 1) + t - 1];
+                const T a0 = rr[((2 * J) & 3) * (P + 2) + t];
+                const T ap = rr[((2 * J + 1) & 3) * (P + 2) + t];
+                const T am = rr[((2 * J - 1) & 3) * (P + 2) + t - 1];
                 gCb[J * sc + t] = a0 + T(0.5) * (ap + am);
             }
         }
@@ -746,61 +744,52 @@ __device__ void walk_down(const Lv<T, W>& L, const Lv<T>& C, T* __restrict__ b, 
         body(Par<0>{}, j);
         body(Par<1>{}, j + 1);
     }
-    __syncthreads();  // z, the updated residual and C.b are complete
+    __syncthreads();  // the updated residual and C.b are complete
 }
 
 // Up-leg of a V(1,1) cycle on level L after the coarser level was solved
 // (its correction e, row stride sc): the black sweep with the correction
-// interpolated at the red neighbours, then the red sweep, reading the down
-// walk's z from xo and writing the new z to xn.  Returns (b, z) over the
-// interior nodes when want_dot.  In a step on row j both phases work on the
-// thread's column of parity j + 1: the black node of row j and the red node
-// of row j - 1.  New values pass through the LDS ring as in walk_down.
+// interpolated at the red neighbours, then the red sweep, writing z to x.
+// Returns (b, z) over the interior nodes when want_dot.  In a step on row j
+// the phases work on the thread's column of parity j + 1: the down-leg's red
+// value b / d of row j + 1 (formed again here, bitwise: the down-leg started
+// from zero), the black node of row j and the red node of row j - 1.  Values
+// pass through the LDS ring as in walk_down.  The walk reads only what no
+// band writes during it (the right-hand side, the weights, the correction).
 template <int BS, bool FINE, typename T, typename W>
 __device__ double walk_up(const Lv<T, W>& L, const T* __restrict__ e, int sc, const T* __restrict__ b,
-                          const T* __restrict__ xo, T* __restrict__ xn, bool want_dot, T* __restrict__ ring,
-                          double* red)
+                          T* __restrict__ x, bool want_dot, T* __restrict__ ring, double* red)
 {
-    const int n = L.n, s = L.s;
+    const int n = L.n, s = L.s, P = n >> 1;
     const WalkRows w = walk_rows<BS>(n);
-    const int j0 = w.j0, j1 = w.j1, ca = 2 * w.t;
+    const int t = w.t, j0 = w.j0, j1 = w.j1, ca = 2 * t;
     const lmem<T> lring = (lmem<T>)ring;
     const lmem<T> zb = lring + w.ring_off;  // new values, 4 rows of s
+    const lmem<T> zd = zb + 4 * s + 1;      // the down-leg's red values, 4 rows of P + 2 from -1
     for (int k = threadIdx.x; k < walk_ring_elems_level(BS, n); k += BS) lring[k] = T(0);
     __syncthreads();
     const gmem<const W> wx = (gmem<const W>)L.wx;
     const gmem<const W> wy = (gmem<const W>)L.wy;
     const gmem<const T> ge = (gmem<const T>)e;
     const gmem<const T> gbv = (gmem<const T>)b;
-    const gmem<const T> xo_ = (gmem<const T>)xo;
-    const gmem<T> xn_ = (gmem<T>)xn;
+    const gmem<T> gx = (gmem<T>)x;
     auto pe = [&](int ii, int jj) -> T {
         const int q = (jj >> 1) * sc + (ii >> 1);
         return (ii & 1) ? T(0.5) * (ge[q] + ge[q + sc + 1]) : ge[q];
     };
-    T b0[2] = {T(0), T(0)}, b1[2] = {T(0), T(0)};  // right-hand side of rows j, j-1
-    double dot = 0.0;
     // As in walk_down, on the finest level each row's weights of the
-    // thread's columns (wx of columns ca-1 .. ca+1 for rows j, j-1; wy of
-    // columns ca, ca+1 for rows j .. j-2) are read from global memory once
-    // and carried in registers; in the FP64 solver so is the down walk's z
-    // of the thread's own two columns (rows j-1 .. j+1), which in the mixed
-    // solver would cost the kernel an occupancy step.
+    // thread's columns (wx of columns ca-1 .. ca+1 for rows j+1 .. j-1; wy of
+    // columns ca, ca+1 for rows j+1 .. j-2) are read from global memory once
+    // and carried in registers.
     constexpr bool win = FINE;
-    constexpr bool zwin = FINE && sizeof(W) < sizeof(T);
-    W x0[3], x1[3], y0[2], y1[2], y2[2];
-    T zm[2], zc[2], zp[2];  // xo of columns ca, ca+1: rows j-1, j, j+1
-    auto WX = [&](int j, int r, int u) -> T {  // wx of row j - r, column ca - 1 + u
-        if constexpr (win) return T(r == 0 ? x0[u] : x1[u]);
-        else return T(wx[(j - r) * s + ca - 1 + u]);
+    W x0[3], x1[3], x2[3], y0[2], y1[2], y2[2], y3[2];
+    auto WX = [&](int j, int r, int u) -> T {  // wx of row j + 1 - r, column ca - 1 + u
+        if constexpr (win) return T(r == 0 ? x0[u] : r == 1 ? x1[u] : x2[u]);
+        else return T(wx[(j + 1 - r) * s + ca - 1 + u]);
     };
-    auto WY = [&](int j, int r, int u) -> T {  // wy of row j - r, column ca + u
-        if constexpr (win) return T(r == 0 ? y0[u] : r == 1 ? y1[u] : y2[u]);
-        else return T(wy[(j - r) * s + ca + u]);
-    };
-    auto XO = [&](int j, int r, int u) -> T {  // xo of row j + r (r = -1, 0, 1), column ca + u
-        if constexpr (zwin) return r < 0 ? zm[u] : r == 0 ? zc[u] : zp[u];
-        else return xo_[(j + r) * s + ca + u];
+    auto WY = [&](int j, int r, int u) -> T {  // wy of row j + 1 - r, column ca + u
+        if constexpr (win) return T(r == 0 ? y0[u] : r == 1 ? y1[u] : r == 2 ? y2[u] : y3[u]);
+        else return T(wy[(j + 1 - r) * s + ca + u]);
     };
     auto load_w = [&](int jj, W* xr, W* yr) {
         const bool in = jj >= 0 && jj <= n - 1;
@@ -811,77 +800,80 @@ __device__ double walk_up(const Lv<T, W>& L, const T* __restrict__ e, int sc, co
         yr[0] = in ? wy[c] : W(0);
         yr[1] = in ? wy[c + 1] : W(0);
     };
-    auto load_z = [&](int jj, T* zr_) {
-        const bool in = jj >= 0 && jj <= n;
-        zr_[0] = in ? xo_[jj * s + ca] : T(0);
-        zr_[1] = in ? xo_[jj * s + ca + 1] : T(0);
-    };
+    T bn[2] = {T(0), T(0)}, b0[2] = {T(0), T(0)}, b1[2] = {T(0), T(0)};  // right-hand side of rows j+1 .. j-1
+    T dn = T(0), d0 = T(0), d1 = T(0);  // the thread's red value of the down-leg, rows j+1 .. j-1
     if constexpr (win) {
-        load_w(j0 - 2, x0, y0);
-        y1[0] = y1[1] = W(0);
-        if constexpr (zwin) {
-            load_z(j0 - 2, zc);
-            load_z(j0 - 1, zp);
-        }
+        load_w(j0 - 3, x0, y0);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) x1[u] = x2[u] = W(0);
+        y1[0] = y1[1] = y2[0] = y2[1] = W(0);
     }
-    auto body = [&](auto par, int j) {
-        constexpr int k = 1 - decltype(par)::value;  // the active column: ca + k
-        b1[0] = b0[0]; b1[1] = b0[1]; b0[0] = T(0); b0[1] = T(0);
+    double dot = 0.0;
+    // k: the active column, ca + k, which holds the red nodes of rows j + 1
+    // and j - 1 and the black node of row j.  ahead: only the red value of
+    // row j + 1 (the steps before the band's first black row)
+    auto body = [&](auto par, int j, auto ahead) {
+        constexpr int k = 1 - decltype(par)::value;
+        b1[0] = b0[0]; b1[1] = b0[1]; b0[0] = bn[0]; b0[1] = bn[1];
+        d1 = d0; d0 = dn;
         if constexpr (win) {
 #pragma unroll
-            for (int u = 0; u < 3; ++u) x1[u] = x0[u];
-            y2[0] = y1[0]; y2[1] = y1[1]; y1[0] = y0[0]; y1[1] = y0[1];
-            load_w(j, x0, y0);
-            if constexpr (zwin) {
-                zm[0] = zc[0]; zm[1] = zc[1]; zc[0] = zp[0]; zc[1] = zp[1];
-                load_z(j + 1, zp);
-            }
+            for (int u = 0; u < 3; ++u) { x2[u] = x1[u]; x1[u] = x0[u]; }
+            y3[0] = y2[0]; y3[1] = y2[1]; y2[0] = y1[0]; y2[1] = y1[1]; y1[0] = y0[0]; y1[1] = y0[1];
+            load_w(j + 1, x0, y0);
         }
         auto Z = [&](int jj, int i) -> T __attribute__((address_space(3)))& { return zb[(jj & 3) * s + i]; };
         const int i = ca + k;
-        if (j == n) {  // the top boundary row, read by the red sweep below it
-            Z(n, ca) = T(0);
-            Z(n, ca + 1) = T(0);
+        // ---- row j+1: its right-hand side and the down-leg's red value
+        const int jn = j + 1;
+        bn[0] = bn[1] = dn = T(0);
+        if (jn >= 1 && jn <= n - 1 && jn <= j1 + 1) {
+            bn[0] = gbv[jn * s + ca];
+            bn[1] = gbv[jn * s + ca + 1];
+            if (i > 0) dn = bn[k] / (WX(j, 0, k) + WX(j, 0, k + 1) + WY(j, 1, k) + WY(j, 0, k));
         }
-        // ---- row j: the black node, corrected
-        if (j >= 1 && j <= n - 1 && j <= j1) {
-            const int c0 = j * s + ca;
-            b0[0] = gbv[c0];
-            b0[1] = gbv[c0 + 1];
-            if (i > 0) {
-                const int c = c0 + k;
-                // the horizontal neighbour outside the pair is the
-                // neighbouring thread's: read from memory (this row, cached)
-                const T xw = k == 0 ? xo_[c - 1] : XO(j, 0, 0);
-                const T xe = k == 0 ? XO(j, 0, 1) : xo_[c + 1];
-                const T nb = WX(j, 0, k) * (xw + pe(i - 1, j)) + WX(j, 0, k + 1) * (xe + pe(i + 1, j))
-                           + WY(j, 1, k) * (XO(j, -1, k) + pe(i, j - 1)) + WY(j, 0, k) * (XO(j, 1, k) + pe(i, j + 1));
-                Z(j, i) = (b0[k] + nb) / (WX(j, 0, k) + WX(j, 0, k + 1) + WY(j, 1, k) + WY(j, 0, k));
+        zd[(jn & 3) * (P + 2) + t] = dn;
+        if constexpr (!decltype(ahead)::value) {
+            if (j == n) {  // the top boundary row, read by the red sweep below it
+                Z(n, ca) = T(0);
+                Z(n, ca + 1) = T(0);
             }
-        }
-        // ---- row j-1: the red node (black neighbours new); the row is then final
-        const int jr = j - 1;
-        if (jr >= j0 && jr < j1) {
-            if (i > 0) {
-                const T lnb = WX(j, 1, k) * Z(jr, i - 1) + WX(j, 1, k + 1) * Z(jr, i + 1) + WY(j, 2, k) * Z(jr - 1, i)
-                            + WY(j, 1, k) * Z(j, i);
-                Z(jr, i) = (b1[k] + lnb) / (WX(j, 1, k) + WX(j, 1, k + 1) + WY(j, 2, k) + WY(j, 1, k));
+            // ---- row j: the black node, corrected.  Its neighbours of row j:
+            // the thread's own red node and the neighbouring thread's
+            if (j >= 1 && j <= n - 1 && j <= j1 && i > 0) {
+                const T out = zd[(j & 3) * (P + 2) + (k == 0 ? t - 1 : t + 1)];
+                const T xw = k == 0 ? out : d0;
+                const T xe = k == 0 ? d0 : out;
+                const T nb = WX(j, 1, k) * (xw + pe(i - 1, j)) + WX(j, 1, k + 1) * (xe + pe(i + 1, j))
+                           + WY(j, 2, k) * (d1 + pe(i, j - 1)) + WY(j, 1, k) * (dn + pe(i, j + 1));
+                Z(j, i) = (b0[k] + nb) / (WX(j, 1, k) + WX(j, 1, k + 1) + WY(j, 2, k) + WY(j, 1, k));
             }
-            const T za = Z(jr, ca), zbb = Z(jr, ca + 1);
-            if (ca > 0) __builtin_nontemporal_store(za, &xn_[jr * s + ca]);
-            __builtin_nontemporal_store(zbb, &xn_[jr * s + ca + 1]);
-            // column 0 is the boundary: its right-hand side entry is never
-            // written and may hold a stale word of another level's layout
-            // (any bit pattern, NaN included), so it stays out of the dot
-            if (want_dot) dot += (ca > 0 ? (double)b1[0] * (double)za : 0.0) + (double)b1[1] * (double)zbb;
+            // ---- row j-1: the red node (black neighbours new); the row is then final
+            const int jr = j - 1;
+            if (jr >= j0 && jr < j1) {
+                if (i > 0) {
+                    const T lnb = WX(j, 2, k) * Z(jr, i - 1) + WX(j, 2, k + 1) * Z(jr, i + 1)
+                                + WY(j, 3, k) * Z(jr - 1, i) + WY(j, 2, k) * Z(j, i);
+                    Z(jr, i) = (b1[k] + lnb) / (WX(j, 2, k) + WX(j, 2, k + 1) + WY(j, 3, k) + WY(j, 2, k));
+                }
+                const T za = Z(jr, ca), zbb = Z(jr, ca + 1);
+                if (ca > 0) __builtin_nontemporal_store(za, &gx[jr * s + ca]);
+                __builtin_nontemporal_store(zbb, &gx[jr * s + ca + 1]);
+                // column 0 is the boundary: its right-hand side entry is never
+                // written and may hold a stale word of another level's layout
+                // (any bit pattern, NaN included), so it stays out of the dot
+                if (want_dot) dot += (ca > 0 ? (double)b1[0] * (double)za : 0.0) + (double)b1[1] * (double)zbb;
+            }
         }
         lds_barrier();  // the walk reads no global value another thread writes
     };
-    // rows j0 - 1 (even) .. j1
+    // rows j0 - 1 (even) .. j1, after the red values of rows j0 - 2 and j0 - 1
+    body(Par<0>{}, j0 - 3, std::true_type{});
+    body(Par<1>{}, j0 - 2, std::true_type{});
 #pragma unroll 1
     for (int j = j0 - 1; j <= j0 + (n / (BS / (n >> 1))); j += 2) {
-        body(Par<0>{}, j);
-        body(Par<1>{}, j + 1);
+        body(Par<0>{}, j, std::false_type{});
+        body(Par<1>{}, j + 1, std::false_type{});
     }
     __syncthreads();  // the new z is complete
     return want_dot ? block_sum<BS>(dot, red) : 0.0;
@@ -1003,29 +995,20 @@ __device__ double vcycle(const Map<T>& M, const Lv<T, W>& F, const T* __restrict
 }
 
 // The V(1,1) cycle with the fused row walks on every level that has them
-// (walk_down / walk_up); the smaller levels keep the separate sweeps.  The
-// finest level's up-leg writes z into zn, which the caller then takes as its
-// z; a walked coarse level keeps its up-leg's result in its coarsening
-// buffer (free after the set-up).  With Q the finest down walk first
-// updates rhs -= alpha Q (and X += alpha Pn).  Returns (rhs, z) when
-// want_dot.
+// (walk_down / walk_up); the smaller levels keep the separate sweeps.  With
+// Q the finest down walk first updates rhs -= alpha Q (and X += alpha Pn).
+// Returns (rhs, z) when want_dot.
 template <int BS, typename T, typename W>
 __device__ double vcycle_walk(const Map<T>& M, const Lv<T, W>& F, T* rhs, const T* Q, T alpha, T* X, const T* Pn,
-                              T* sol, T* zn, bool want_dot, double* red)
+                              T* sol, bool want_dot, double* red)
 {
     const int l = M.l;
     constexpr int Lc = kExactCoarse<T> ? 2 : 1;
-    auto walked = [&](int L) { return walk_level<BS>(1 << L, 1); };
-    auto result = [&](int L) {  // level L's z after its up-leg
-        Lv<T> V = coarse_level(M, L);
-        if (walked(L)) V.x = V.kap;
-        return V;
-    };
-    walk_down<BS, true>(F, coarse_level(M, l - 1), rhs, Q, alpha, sol, X, Pn, M.ring);
+    walk_down<BS, true>(F, coarse_level(M, l - 1), rhs, Q, alpha, X, Pn, M.ring);
     for (int Lk = l - 1; Lk > Lc; --Lk) {
         const Lv<T> L = coarse_level(M, Lk);
-        if (walked(Lk))
-            walk_down<BS, false>(L, coarse_level(M, Lk - 1), L.b, (const T*)nullptr, T(0), L.x, (T*)nullptr,
+        if (walk_level<BS>(1 << Lk, 1))
+            walk_down<BS, false>(L, coarse_level(M, Lk - 1), L.b, (const T*)nullptr, T(0), (T*)nullptr,
                           (const T*)nullptr, M.ring);
         else
             down_step<BS>(L, coarse_level(M, Lk - 1), L.b, L.x, 1, false);
@@ -1044,18 +1027,18 @@ __device__ double vcycle_walk(const Map<T>& M, const Lv<T, W>& F, T* rhs, const 
     }
     for (int Lk = Lc + 1; Lk <= l - 1; ++Lk) {
         const Lv<T> L = coarse_level(M, Lk);
-        const Lv<T> Cc = result(Lk - 1);
-        if (walked(Lk)) walk_up<BS, false>(L, Cc.x, Cc.s, L.b, L.x, L.kap, false, M.ring, red);
-        else up_step<BS>(L, Cc, L.b, L.x, 1, false, red);
+        const Lv<T> C = coarse_level(M, Lk - 1);
+        if (walk_level<BS>(1 << Lk, 1)) walk_up<BS, false>(L, C.x, C.s, L.b, L.x, false, M.ring, red);
+        else up_step<BS>(L, C, L.b, L.x, 1, false, red);
     }
-    const Lv<T> Cf = result(l - 1);
-    return walk_up<BS, true>(F, Cf.x, Cf.s, rhs, sol, zn, want_dot, M.ring, red);
+    const Lv<T> C = coarse_level(M, l - 1);
+    return walk_up<BS, true>(F, C.x, C.s, rhs, sol, want_dot, M.ring, red);
 }
 
 // ------------------------------------------------------- setup & obs --
 template <int BS, typename T, typename KT>
 __device__ void setup_hierarchy(const Map<T>& M, const Lv<T>& F, const KT* __restrict__ kap,
-                                float* wx32 = nullptr, float* wy32 = nullptr, bool walks = false)
+                                float* wx32 = nullptr, float* wy32 = nullptr)
 {
     const int l = M.l;
     edge_weights<BS>(kap, F.wx, F.wy, F.n, F.lg, wx32, wy32);
@@ -1070,11 +1053,6 @@ __device__ void setup_hierarchy(const Map<T>& M, const Lv<T>& F, const KT* __res
             if (L >= 2) coarsen_kappa<BS>(V.kap, coarse_level(M, L - 1).kap, L - 1);
             __syncthreads();
         }
-        // a walked level's coefficients are dead now: the buffer takes the
-        // up-leg's z, whose boundary must read zero
-        if (walks)
-            for (int L = l - 1; L >= 8; --L)
-                if (walk_level<BS>(1 << L, 1)) zero_boundary<BS>(coarse_level(M, L).kap, 1 << L);
         __syncthreads();
     }
 }
@@ -1180,15 +1158,13 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
     const double h2 = 1.0 / (double)(F.n * F.n);
     const double* kap = (const double*)J.kap;
     // WK = 2 instances run the fused row walks (their launch guarantees a
-    // walked level, V(1,1) and the LDS ring); the new z goes to Q's array,
-    // and the two swap after every cycle
+    // walked level, V(1,1) and the LDS ring)
     constexpr bool walks = WK == 2;
     zero_boundary<BS>(X, F.n);
     zero_boundary<BS>(Z, F.n);
     zero_boundary<BS>(Pb[0], F.n);
     zero_boundary<BS>(Pb[1], F.n);
-    if (walks) zero_boundary<BS>(Q, F.n);
-    setup_hierarchy<BS>(M, F, kap, FV.wx, FV.wy, walks);
+    setup_hierarchy<BS>(M, F, kap, FV.wx, FV.wy);
     if (l == 2) build_coarse_inverse<BS>(FV, M.cinv);
     else if (l >= 3) build_coarse_inverse<BS>(coarse_level(M, 2), M.cinv);
     // The forward map needs the solution only at the observation points
@@ -1206,9 +1182,8 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
         for (int o = threadIdx.x; o < C.nobs; o += BS) J.G[o] = 0.0;
     __syncthreads();
     if (walks) {
-        vcycle_walk<BS>(M, FV, R, (const double*)nullptr, 0.0, (double*)nullptr, (const double*)nullptr, Z, Q,
+        vcycle_walk<BS>(M, FV, R, (const double*)nullptr, 0.0, (double*)nullptr, (const double*)nullptr, Z,
                         false, red);
-        double* t_ = Z; Z = Q; Q = t_;
     } else {
         vcycle<BS>(M, FV, R, Z, C.nu, false, false, red);
     }
@@ -1257,8 +1232,7 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
         if (!keep_x) observe_step<BS>(J, C, Pn, alpha);
         double rzn;
         if (walks) {  // the r update rides on the down walk
-            rzn = vcycle_walk<BS>(M, FV, R, Q, alpha, (double*)nullptr, (const double*)nullptr, Z, Q, true, red);
-            double* t_ = Z; Z = Q; Q = t_;
+            rzn = vcycle_walk<BS>(M, FV, R, Q, alpha, (double*)nullptr, (const double*)nullptr, Z, true, red);
         } else {
             // the r update fused with the first red sweep of the V-cycle
             MLS_FOR_INTERIOR(F, {
@@ -1316,8 +1290,7 @@ __device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common&
     zero_boundary<BS>(Pb[0], F.n);
     zero_boundary<BS>(Pb[1], F.n);
     zero_boundary<BS>(X64, F.n);
-    if (walks) zero_boundary<BS>(Q, F.n);
-    setup_hierarchy<BS>(M, F, kap, nullptr, nullptr, walks);
+    setup_hierarchy<BS>(M, F, kap);
     MLS_FOR_INTERIOR(F, { X64[c] = 0.0; X[c] = 0.f; R[c] = (float)h2; })
     __syncthreads();
     // x64 += x32, x32 = 0, then r = b - A x64 in FP64 (rounded to FP32)
@@ -1337,10 +1310,8 @@ __device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common&
     };
     auto precondition = [&]() {  // z = V r and (r, z)
         if (walks) {
-            const double d = vcycle_walk<BS>(M, F, R, (const float*)nullptr, 0.f, (float*)nullptr,
-                                             (const float*)nullptr, Z, Q, true, red);
-            float* t_ = Z; Z = Q; Q = t_;
-            return d;
+            return vcycle_walk<BS>(M, F, R, (const float*)nullptr, 0.f, (float*)nullptr, (const float*)nullptr, Z,
+                                   true, red);
         }
         vcycle<BS>(M, F, R, Z, C.nu, false, false, red);
         double rz = 0.0;
@@ -1378,8 +1349,7 @@ __device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common&
         const float alpha = (float)(rz / pq);
         double rzn;
         if (walks) {  // the x and r updates ride on the down walk
-            rzn = vcycle_walk<BS>(M, F, R, Q, alpha, X, Pn, Z, Q, true, red);
-            float* t_ = Z; Z = Q; Q = t_;
+            rzn = vcycle_walk<BS>(M, F, R, Q, alpha, X, Pn, Z, true, red);
         } else {
             MLS_FOR_INTERIOR(F, {
                 X[c] += alpha * Pn[c];
