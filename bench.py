@@ -108,15 +108,20 @@ def tuned_matches(rec):
     return same_dev and rec.get("solver_source_sha256_16") == solver_sha()
 
 
-# On these levels the library's own launch choice is the register-resident
-# solver, several times faster than any shape of the general one; the
-# committed shapes of those levels apply only when a file is given by hand.
+# On these levels (and in FP64 on the Dirichlet problem at h = 1/128) the
+# library's own launch choice is the register-resident solver, several times
+# faster than any shape of the general one; the committed shapes of those
+# levels apply only when a file is given by hand.
 RESIDENT_LEVELS = range(3, 7)
+
+
+def resident_level(form, l, nobs):
+    return l in RESIDENT_LEVELS or (form == "fp64" and l == 7 and nobs <= 128)
 
 
 def runs_resident(ctx, l):
     grid, block, nu, lds = ctx.get_launch(l)
-    return l in RESIDENT_LEVELS and grid == 0 and lds == 0 and (nu == 0 or (block == 0 and nu == 1))
+    return resident_level("fp64", l, ctx.nobs) and grid == 0 and lds == 0 and (nu == 0 or (block == 0 and nu == 1))
 
 
 def resident_bytes(l, nobs, particles):
@@ -136,7 +141,7 @@ def load_tuned(path, ctxs):
         return None
     for form, c in ctxs.items():
         for lv, sh in rec.get(form, {}).items():
-            if int(lv) in RESIDENT_LEVELS:
+            if resident_level(form, int(lv), c.nobs):
                 continue
             c.set_launch(int(lv), sh["grid"], sh["block"], sh.get("nu", 0), sh.get("lds", 0))
     return path

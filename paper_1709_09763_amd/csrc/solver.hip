@@ -1660,7 +1660,8 @@ static bool launch_walks(int l, int bs, int nu)
 int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
 {
     if (a.N == 0) return MLS2MC_OK;
-    if (resident_level(ctx, a.l)) return launch_resident(ctx, a, s);
+    // (at h = 1/128 the resident solver does not keep the field)
+    if (resident_level(ctx, a.l) && !(a.l == 7 && a.p_out)) return launch_resident(ctx, a, s);
     if (ctx->prob.bc == MLS2MC_BC_FLOW_CELL) return launch_flow_solve(ctx, a, s);
     const int l = a.l;
     const bool mixed = a.kappa_f32;
@@ -1969,6 +1970,7 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
             list_shape(ctx, gr.lmax, gr.total, mixed, &grid, &slot, &bs);
             ws_need = std::max(ws_need, (size_t)grid * slot * esz);
         }
+        for (const ListLevel& lv : lc.levels) ws_need = std::max(ws_need, resident_workspace(ctx, lv.l, lv.total));
         out.push_back(lc);
         off += (bytes + 255) & ~size_t(255);
     }
