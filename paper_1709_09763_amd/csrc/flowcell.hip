@@ -29,6 +29,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "lanes.h"
 #include "walks.h"
 
 namespace mls {
@@ -456,8 +457,11 @@ extern __shared__ __align__(16) double flow_lds[];
 // n + 1 unknown rows, and thread i of a group owns column i of its band,
 // keeping p and WY of the row below and of its own row in registers, so
 // each row of Z, P_old and WY is loaded once per pass rather than three
-// times.  Lane 0 of a group owns the Dirichlet column x1 = 0 and idles; the
-// ghost rows below and above carry zero weights, as in the row loop.
+// times; the neighbours in the row are the adjacent lanes' (a wave's end lanes
+// load theirs), and a row's loads are asked for one row ahead (the Dirichlet
+// solver's walk_apply has the measurements).  Lane 0 of a group owns the
+// Dirichlet column x1 = 0, which holds zeros, and stores nothing; the ghost rows
+// below and above carry zero weights, as in the row loop.
 __device__ __forceinline__ int flow_opaque(int c)  // keeps one 32-bit offset for all arrays
 {
     asm("" : "+v"(c));
@@ -469,26 +473,53 @@ __device__ double flow_walk_apply(const FLv& F, const double* __restrict__ Z, co
                                   double beta, double* __restrict__ Pn, double* __restrict__ Q)
 {
     const int n = F.n, s = F.s, m = BS / n;
-    const int i = threadIdx.x & (n - 1), band = threadIdx.x / n;
+    const int i = threadIdx.x & (n - 1), band = threadIdx.x / n, lane = threadIdx.x & 63;
     const int rows = (n + m) / m;  // ceil((n + 1) / m)
     const int j0 = band * rows, j1 = min(n + 1, j0 + rows);
     double pq = 0.0;
-    if (i == 0 || j0 >= j1) return pq;
-    auto pn = [&](int q) { return Z[q] + beta * Po[q]; };
+    if (j0 >= j1) return pq;
+    const bool first = lane == 0, last = lane == 63;
     const int c0 = j0 * s + i;  // the row below unknown row j0
-    double pm = pn(c0), p0 = pn(c0 + s), wym = F.wy[c0];
+    double pm = Z[c0] + beta * Po[c0], p0 = Z[c0 + s] + beta * Po[c0 + s], wym = F.wy[c0];
+    struct Row {
+        double z, o, wx, wy, ze, oe, we;
+    } next = {};
+    auto load = [&](int j) {  // what row j's step reads
+        const int c = flow_opaque((j + 1) * s + i);
+        next.z = Z[c + s];
+        next.o = Po[c + s];
+        next.wx = F.wx[c];
+        next.wy = F.wy[c];
+        if (first || last) {
+            const int e = c + (first ? -1 : 1);
+            next.ze = Z[e];
+            next.oe = Po[e];
+            next.we = F.wx[c - 1];
+        }
+    };
+    load(j0);
 #pragma unroll 1
     for (int j = j0; j < j1; ++j) {
         const int c = flow_opaque((j + 1) * s + i);
-        const double pp = pn(c + s), wyc = F.wy[c];
-        const double nb = F.wx[c - 1] * pn(c - 1) + F.wx[c] * pn(c + 1) + wym * pm + wyc * pp;
-        const double qv = (F.wx[c - 1] + F.wx[c] + wym + wyc) * p0 - nb;
-        Pn[c] = p0;
-        Q[c] = qv;
-        pq += p0 * qv;
+        const Row r = next;
+        load(min(j + 1, j1 - 1));
+        const double pp = r.z + beta * r.o, pe = r.ze + beta * r.oe;
+        double pw = west(p0), px = east(p0), wxw = west(r.wx);
+        if (first) {
+            pw = pe;
+            wxw = r.we;
+        }
+        if (last) px = pe;
+        const double nb = wxw * pw + r.wx * px + wym * pm + r.wy * pp;
+        const double qv = (wxw + r.wx + wym + r.wy) * p0 - nb;
+        if (i > 0) {
+            Pn[c] = p0;
+            Q[c] = qv;
+            pq += p0 * qv;
+        }
         pm = p0;
         p0 = pp;
-        wym = wyc;
+        wym = r.wy;
     }
     return pq;
 }

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "lanes.h"
 #include "resident.h"
 #include "walks.h"
 
@@ -331,8 +332,11 @@ __device__ void coarsen_kappa(const KT* __restrict__ kf, T* __restrict__ kc, int
 // rows, and thread i of a group owns column i of its band and walks it
 // upward, keeping p and WY of the row below and of its own row in
 // registers.  Each row of Z, P_old and WY is then loaded once per pass
-// rather than three times (plus one row at each band's start).  Lane 0 of a
-// group owns the boundary column and idles.  With m = 1 the row loop gives
+// rather than three times (plus one row at each band's start).  The
+// neighbours in the row are the adjacent lanes' p and WX (a wave lies within
+// one row); only a wave's end lanes load theirs, which halves the pass's
+// load instructions.  Lane 0 of a group owns the boundary column, which holds
+// zeros, and stores nothing.  With m = 1 the row loop gives
 // thread i the same nodes in the same order, and the walk evaluates the
 // same expressions, so the results are bitwise the row loop's; with m > 1
 // only the order of the inner product's terms differs.  (The Gauss-Seidel
@@ -353,41 +357,77 @@ __device__ __forceinline__ int opaque(int c)
 // p = z + beta p_old formed on the fly at the node and its neighbours,
 // stored to Pn with q = A p; returns this thread's share of (p, q).  With X
 // the pass also applies the pending x += xa p_old at its nodes.
+//
+// What bounds the pass on the large levels is the latency of a row's loads, with
+// one workgroup per CU: the FP64 form asks for the next row's before it forms
+// this one (h = 1/256, 256 particles: 257 us a pass with neighbours loaded, 222
+// with the lanes' values, 163 with the row ahead too, the rate of a copy;
+// the mixed form 154, 105 and 132: it waits less and spills more).
 template <int BS, bool NT, typename T>
 __device__ double walk_apply(const Lv<T>& F, const T* __restrict__ Z, const T* __restrict__ Po, T beta,
                              T* __restrict__ Pn, T* __restrict__ Q, T* __restrict__ X = nullptr, T xa = T(0))
 {
+    constexpr bool AHEAD = sizeof(T) == 8;
     const int n = F.n, s = F.s, m = BS / n;
-    const int i = threadIdx.x & (n - 1), band = threadIdx.x / n;
+    const int i = threadIdx.x & (n - 1), band = threadIdx.x / n, lane = threadIdx.x & 63;
     const int rows = (n - 2 + m) / m;  // ceil((n - 1) / m)
     const int j0 = 1 + band * rows, j1 = min(n, j0 + rows);
     double pq = 0.0;
-    if (i == 0 || j0 >= j1) return pq;
-    auto pn = [&](int q) { return fma(beta, Po[q], Z[q]); };
+    if (j0 >= j1) return pq;
+    const bool first = lane == 0, last = lane == 63;
     const int c0 = (j0 - 1) * s + i;
-    T pm = pn(c0), p0 = pn(c0 + s), wym = F.wy[c0];
+    T pm = fma(beta, Po[c0], Z[c0]), p0 = fma(beta, Po[c0 + s], Z[c0 + s]), wym = F.wy[c0];
+    // what the step of a row reads: Z and P_old of the row above, the row's
+    // weights, and the end lanes' outer neighbours
+    struct Row {
+        T z, o, wx, wy, ze, oe, we;
+    } next = {};
+    auto load = [&](int j) {
+        const int c = opaque(j * s + i);
+        next.z = Z[c + s];
+        next.o = Po[c + s];
+        next.wx = F.wx[c];
+        next.wy = F.wy[c];
+        if (first || last) {
+            const int e = c + (first ? -1 : 1);
+            next.ze = Z[e];
+            next.oe = Po[e];
+            next.we = F.wx[c - 1];
+        }
+    };
+    if constexpr (AHEAD) load(j0);
 #pragma unroll 1
     for (int j = j0; j < j1; ++j) {
         const int c = opaque(j * s + i);
-        const T pp = pn(c + s), wyc = F.wy[c];
-        const T v = (F.wx[c - 1] + F.wx[c] + wym + wyc) * p0
-                  - (F.wx[c - 1] * pn(c - 1) + F.wx[c] * pn(c + 1) + wym * pm + wyc * pp);
-        if constexpr (NT) {
-            // on the walked levels p and q are read again only in later
-            // passes: streaming stores keep them from pushing the rows the
-            // walks reuse out of the L2 (on smaller levels they stay in the
-            // caches until then, and plain stores are faster)
-            __builtin_nontemporal_store(p0, &Pn[c]);
-            __builtin_nontemporal_store(v, &Q[c]);
-        } else {
-            Pn[c] = p0;
-            Q[c] = v;
+        if constexpr (!AHEAD) load(j);
+        const Row r = next;
+        if constexpr (AHEAD) load(min(j + 1, j1 - 1));
+        const T pp = fma(beta, r.o, r.z), pe = fma(beta, r.oe, r.ze);
+        T pw = west(p0), px = east(p0), wxw = west(r.wx);
+        if (first) {
+            pw = pe;
+            wxw = r.we;
         }
-        if (X) X[c] += xa * Po[c];
-        pq += (double)p0 * (double)v;
+        if (last) px = pe;
+        const T v = (wxw + r.wx + wym + r.wy) * p0 - (wxw * pw + r.wx * px + wym * pm + r.wy * pp);
+        if (i > 0) {
+            if constexpr (NT) {
+                // on the walked levels p and q are read again only in later
+                // passes: streaming stores keep them from pushing the rows the
+                // walks reuse out of the L2 (on smaller levels they stay in the
+                // caches until then, and plain stores are faster)
+                __builtin_nontemporal_store(p0, &Pn[c]);
+                __builtin_nontemporal_store(v, &Q[c]);
+            } else {
+                Pn[c] = p0;
+                Q[c] = v;
+            }
+            if (X) X[c] += xa * Po[c];
+            pq += (double)p0 * (double)v;
+        }
         pm = p0;
         p0 = pp;
-        wym = wyc;
+        wym = r.wy;
     }
     return pq;
 }
