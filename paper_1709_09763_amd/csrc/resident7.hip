@@ -24,65 +24,33 @@
 // nontemporal loads of the coefficients 356 / 726 / 2698; the h = 1/64 weights
 // held through the visit of h = 1/32 362 / 697 / 2523.
 //
-//  * Two columns per thread: with a = 2 lane and b = a + 1, row k has one
-//    node of each colour, red in column a where k is even.  No lane is idle
-//    and no select depends on the lane.  A node's horizontal neighbours are
-//    the thread's own other column and one adjacent lane.
-//  * A strip exchanges its first and last row's values of one colour with
-//    the strips above and below (the edge's weight is the lower strip's, which
-//    sends the product).
-//  * After the down-leg nothing of z is kept: the up-leg forms the red values
-//    again from r, and the black ones are swept anyway.
-//  * The coarse level h = 1/64 has column I = lane in the same threads, eight
-//    rows each, so restriction and prolongation stay in registers but for one
-//    value per thread.  The levels from h = 1/32 down are those
-//    of resident.hip.
-//  * The solution is not kept: the thread that owns an observation's node
-//    adds alpha p there (so launches that ask for the field, and those with
-//    more observations than the LDS list holds, stay with the general
-//    solver).
+// The V-cycle is cycle7 of strips7.h, which explains the layout.
+//
+// The solution is not kept: the thread that owns an observation's node adds
+// alpha p there (so launches that ask for the field, and those with more
+// observations than the LDS list holds, stay with the general solver).
 #include <algorithm>
-#include <type_traits>
 
 #include "resident.h"
-#include "strips.h"
+#include "strips7.h"
 
 namespace mls {
 
 namespace {
 
-constexpr int kN = 128, kNT = 512, kR = 16;  // nodes per side, threads, rows per thread
-constexpr int kObs = 128;                    // observations that the LDS list holds
-constexpr int kAhead = 2;                    // rows whose weights are asked for ahead of their use
-constexpr int kLdsRows = 10;                 // rows of each strip whose FP32 edges stay in the LDS
-using G6 = Geo<6, 4, kNT, false>;
-using G5 = Geo<5, 1, kNT, false>;
-using G4 = Geo<4, 2, 64, false>;
-using G3 = Geo<3, 1, 64, false>;
+constexpr int kN = 128, kNT = 512, kR = kRows7<kNT>;  // nodes per side, threads, rows per thread
+constexpr int kObs = 128;                             // observations that the LDS list holds
+constexpr int kLdsRows = 10;                          // rows of each strip whose FP32 edges stay in the LDS
 
 struct Mem7 {
-    // Exchange, one value per thread: a1, a2 and in rs6 also a3 and a0, which
-    // are not in use between the restriction onto h = 1/32 and the h = 1/32
-    // level's solution, whose place rs6 is.  The coarse levels' exchange
-    // reads up to one strip outside a1 and a2, with zero weight.
-    double pad[64];
-    double a1[kNT], a2[kNT];
-    static constexpr int sol_len = grid_rows<G6, G5> * 32, sol_off = G6::rs - sol_len;
-    double rs6[G6::rs + 33];
+    Exchange7<double, kNT> x;
     float4 e[kLdsRows][kNT];  // set-up: the h = 1/64 coefficients
-    CoarseMem<double, 5, 1, kNT, false> c5;
-    CoarseMem<double, 4, 2, 64, false> c4;
-    CoarseMem<double, 3, 1, 64, false> c3;
-    double e4[(grid_rows<G5, G4> + 1) * 16 + 1];
-    double e3[(grid_rows<G4, G3> + 1) * 8 + 1];
-    double e2[(G3::pairs + 1) * 4 + 1];
-    double cinv[81];
+    Levels5<double> low;
     double red[2][16];
-    double obsx[3 * kObs];  // the solution at the observations' nodes
+    double obsx[3 * kObs];          // the solution at the observations' nodes
     unsigned short node[3 * kObs];  // where an observation's node is in obsx (0xffff: on the boundary)
     int64_t draw;
 };
-static_assert(G6::rs >= 2 * kNT, "a3 and a0 fit in rs6, before its trailing zeros");
 static_assert(sizeof(float4) * kLdsRows * kNT >= sizeof(double) * 2 * 64 * 64, "the h = 1/64 coefficients fit in e");
 
 // The workgroup's slot: a part per wave, so that a lane reaches all of its
@@ -92,14 +60,6 @@ constexpr int kWaveInv = (kR - kLdsRows) * 64 * 2;
 constexpr int kWaveC6 = kWaveInv + 2 * kR * 64;
 constexpr int kWave = kWaveC6 + kW * (kR / 4) * 64;
 constexpr int64_t kSlot = (int64_t)kWave * (kNT / 64);
-
-// a value that the compiler forms again at each use instead of holding what
-// follows from it (addresses) through the loops
-__device__ __forceinline__ int again(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
 
 struct Params7 {
     int64_t N;
@@ -127,8 +87,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
     const int t0 = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(t0 >> 6);
     constexpr int n = kN;
-    double* a0 = m.rs6 + kNT;
-    double* a3 = m.rs6;
+    double* a0 = m.x.rs6 + kNT;
+    double* a3 = m.x.rs6;
     double* slot = A.ws + blockIdx.x * kSlot + wv * kWave;
     float4* eg = reinterpret_cast<float4*>(slot);
     double* w6 = slot + kWaveC6;
@@ -139,8 +99,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
     int obs_at = 0;
     {
         const int t = t0;
-        unsigned* bits = reinterpret_cast<unsigned*>(m.a1);
-        int* at = reinterpret_cast<int*>(m.a2);
+        unsigned* bits = reinterpret_cast<unsigned*>(m.x.a1);
+        int* at = reinterpret_cast<int*>(m.x.a2);
         int* count = at + kNT;
         bits[t] = 0;
         if (t == 0) *count = 0;
@@ -203,41 +163,18 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
             up = c[1];
         };
         double* k6 = reinterpret_cast<double*>(m.e);
-        double* k5 = m.rs6;
+        double* k5 = m.x.rs6;
         coarsen<double, 6, kNT>(k6, t, fine_cell);
         auto clear = [&](double* a, int c) { for (int k = t; k < c; k += kNT) a[k] = 0.0; };
-        clear(m.pad, 64);
-        clear(m.a1, 2 * kNT);  // a1 and a2
-        clear(m.e2, sizeof(m.e2) / 8);
-        clear(m.e3, sizeof(m.e3) / 8);
-        clear(m.e4, sizeof(m.e4) / 8);
         clear(m.obsx, 3 * A.nobs);
         group_order();
-#define MLS_LDS_CELL(K, w)                                  \
-    [&](int ci, int cj, double& lo, double& up) {           \
-        lo = (K)[2 * (cj * (w) + ci)];                      \
-        up = (K)[2 * (cj * (w) + ci) + 1];                  \
-    }
-        {
-            Weights<double, kR / 4> W;
-            make_weights<true, G6>(W, t, MLS_LDS_CELL(k6, 64));
-            store_weights<double, kR / 4, 64>(W, w6, lane);
-        }
-        coarsen<double, 5, kNT>(k5, t, MLS_LDS_CELL(k6, 64));
+        weights6<double, kNT>(w6, k6, t);
+        coarsen<double, 5, kNT>(k5, t, [&](int ci, int cj, double& lo, double& up) {
+            lo = k6[2 * (cj * 64 + ci)];
+            up = k6[2 * (cj * 64 + ci) + 1];
+        });
         group_order();
-        coarse_weights(m.c5, k5, t);
-        if (wv == 0) {
-            coarsen<double, 4, 64>(m.c5.rs, t, MLS_LDS_CELL(k5, 32));
-            wave_order();
-            coarse_weights(m.c4, m.c5.rs, t);
-            coarsen<double, 3, 64>(m.c4.rs, t, MLS_LDS_CELL(m.c5.rs, 16));
-            wave_order();
-            coarse_weights(m.c3, m.c4.rs, t);
-            coarsen<double, 2, 64>(m.c3.rs, t, MLS_LDS_CELL(m.c4.rs, 8));
-            wave_order();
-            exact_build<false>(m.c3.rs, m.cinv, t);
-        }
-#undef MLS_LDS_CELL
+        build_levels5(m.low, k5, t);
         // the finest level's V-cycle weights: FP32 edges x (a - b), y (b - east
         // a), z (a, to the row above), w (b, to the row above); FP64 inverse
         // diagonals of rows k, k + 1 in one pair: [k / 2][colour]
@@ -283,10 +220,9 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
             }
         }
         group_order();
-        clear(m.rs6, G6::rs + 33);  // out of the coefficients' use
-        clear(m.c5.rs, sizeof(m.c5.rs) / 8);
-        clear(m.c4.rs, sizeof(m.c4.rs) / 8);
-        clear(m.c3.rs, sizeof(m.c3.rs) / 8);
+        // also the exchange, out of the coefficients' use
+        clear(m.x.pad, sizeof(m.x) / 8);
+        clear_levels5<double, kNT>(m.low, t);
         group_order();
 
         auto edge = [&](int k, int u) -> float4 {
@@ -304,34 +240,6 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
             for (int k = 0; k < kNT / 64; ++k) s += m.red[which][k];
             return read_lane(s, 0);
         };
-        // neighbour sums of colour C (0: red) from the other colour's X; dn:
-        // the product from the strip below, up: the value of the one above
-        auto sums = [&](auto C, const double (&X)[kR], double dn, double up, auto use) {
-            constexpr int c = decltype(C)::value;
-            const int u = again(t0);
-            float4 w[kR];
-            double d[kR];
-            double below = dn;
-#pragma unroll
-            for (int k = 0; k < kAhead; ++k) { w[k] = edge(k, u); d[k] = inv(k, c, u); }
-#pragma unroll
-            for (int k = 0; k < kR; ++k) {
-                if (k + kAhead < kR) {
-                    w[k + kAhead < kR ? k + kAhead : 0] = edge(k + kAhead, u);
-                    d[k + kAhead < kR ? k + kAhead : 0] = inv(k + kAhead, c, u);
-                }
-                const bool col_b = (k & 1) == (c == 0);  // this colour's column in row k
-                const double v = (double)(col_b ? w[k].w : w[k].z);
-                const double hw = (double)w[k].y;
-                const double far = col_b ? hw * east(X[k]) : west(hw * X[k]);
-                const double nxt = k + 1 < kR ? X[k + 1 < kR ? k + 1 : 0] : up;
-                use(k, ((double)w[k].x * X[k] + far) + (v * nxt + below), d[k]);
-                below = (double)(col_b ? w[k].z : w[k].w) * X[k];  // X's node: the other column
-            }
-        };
-        using Red = std::integral_constant<int, 0>;
-        using Black = std::integral_constant<int, 1>;
-
         // ---- state
         double rr[kR], rb[kR], pr[kR], pb[kR], zr[kR], zb[kR];
         const double h2 = 1.0 / (double)(n * n);
@@ -345,94 +253,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
         }
 
         auto vcycle = [&]() -> double {
-            {
-                const int t = again(t0);
-                const float4 e7 = edge(kR - 1, t);
-#pragma unroll
-                for (int k = 0; k < kR; ++k) zr[k] = rr[k] * inv(k, 0, t);
-                a0[t] = (double)e7.w * zr[kR - 1];
-                m.a1[t] = zr[0];
-            }
-            group_order();
-            int t = again(t0), lane = t & 63;
-            sums(Black(), zr, wv > 0 ? a0[t - 64] : 0.0, wv < kNT / 64 - 1 ? m.a1[t + 64] : 0.0,
-                 [&](int k, double s, double d) { zb[k] = (rb[k] + s) * d; });
-            m.a2[t] = (double)edge(kR - 1, t).z * zb[kR - 1];
-            a3[t] = zb[0];
-            group_order();
-            // the red residual
-            sums(Red(), zb, wv > 0 ? m.a2[t - 64] : 0.0, wv < kNT / 64 - 1 ? a3[t + 64] : 0.0,
-                 [&](int k, double s, double) { zr[k] = s; });
-            a0[t] = zr[kR - 1];
-            group_order();
-            double E[kR / 2 + 1];
-            {
-                constexpr int P6 = kR / 4;
-                const bool e = lane & 1;
-                double br[P6], bb[P6], yr[P6], yb[P6];
-                {
-                    // the diagonal's lower end, column 2 lane - 1: of the
-                    // adjacent lane (lane 0 is the boundary column)
-                    const double q0 = wv > 0 ? a0[t - 65] : 0.0;
-                    double b[kR / 2];
-#pragma unroll
-                    for (int J = 0; J < kR / 2; ++J)
-                        b[J] = zr[2 * J] + 0.5 * (zr[2 * J + 1] + (J ? west(zr[J ? 2 * J - 1 : 0]) : q0));
-                    const At<G6, P6, true> at;
-                    Weights<double, P6> W;
-                    load_weights<double, P6, 64>(W, w6, again(t0) & 63);
-#pragma unroll
-                    for (int k = 0; k < P6; ++k) {
-                        br[k] = pick(e, b[2 * k + 1], b[2 * k]);
-                        bb[k] = pick(e, b[2 * k], b[2 * k + 1]);
-                        yr[k] = br[k] * W.inv[0][k];
-                    }
-                    down_leg<G6, kNT>(W, at, bb, yr, yb, m.a1, m.a2, m.rs6);
-                }
-                group_order();
-                double* sol5 = m.rs6 + Mem7::sol_off;
-                coarse_visit<5, 1, kNT, false, true>(m.rs6, m.c5, sol5, m.e4, m.a1, m.a2, [&]() {
-                    if (wv == 0)
-                        coarse_visit<4, 2, 64, false, true>(m.c5.rs, m.c4, m.e4, m.e3, m.a1, m.a2, [&]() {
-                            coarse_visit<3, 1, 64, false, true>(m.c4.rs, m.c3, m.e3, m.e2, m.a1, m.a2, [&]() {
-                                exact_solve<false>(m.c3.rs, m.cinv, m.e2, again(t0));
-                            });
-                        });
-                });
-                group_order();
-                {
-                    const At<G6, P6, true> at;
-                    Weights<double, P6> W;
-                    load_weights<double, P6, 64>(W, w6, again(t0) & 63);
-                    up_leg<G6, kNT>(W, at, br, bb, yr, yb, m.a1, m.a2, sol5);
-                }
-#pragma unroll
-                for (int k = 0; k < P6; ++k) {
-                    E[2 * k] = pick(e, yb[k], yr[k]);
-                    E[2 * k + 1] = pick(e, yr[k], yb[k]);
-                }
-                a3[t] = E[0];
-            }
-            t = again(t0);
-            lane = t & 63;
-            const float4 e7 = edge(kR - 1, t);
-            group_order();
-            E[kR / 2] = wv < kNT / 64 - 1 && lane < 63 ? a3[t + 65] : 0.0;  // of the strip above, next column
-#pragma unroll
-            for (int J = 0; J < kR / 2; ++J) {
-                zr[2 * J] = rr[2 * J] * inv(2 * J, 0, t) + E[J];
-                zr[2 * J + 1] = rr[2 * J + 1] * inv(2 * J + 1, 0, t) + 0.5 * (E[J] + (J + 1 < kR / 2 ? east(E[J + 1]) : E[kR / 2]));
-            }
-            a0[t] = (double)e7.w * zr[kR - 1];
-            m.a1[t] = zr[0];
-            group_order();
-            sums(Black(), zr, wv > 0 ? a0[t - 64] : 0.0, wv < kNT / 64 - 1 ? m.a1[t + 64] : 0.0,
-                 [&](int k, double s, double d) { zb[k] = (rb[k] + s) * d; });
-            m.a2[t] = (double)edge(kR - 1, t).z * zb[kR - 1];
-            a3[t] = zb[0];
-            group_order();
-            sums(Red(), zb, wv > 0 ? m.a2[t - 64] : 0.0, wv < kNT / 64 - 1 ? a3[t + 64] : 0.0,
-                 [&](int k, double s, double d) { zr[k] = (rr[k] + s) * d; });
+            cycle7<double, kNT>(rr, rb, zr, zb, edge, inv, w6, m.x, m.low, t0, wv);
             double d = 0.0;
 #pragma unroll
             for (int k = 0; k < kR; ++k) d += rr[k] * zr[k] + rb[k] * zb[k];
@@ -468,8 +289,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
             // the last row's column b is red, row 0's column a
             const int t = again(t0), lane = t & 63;
             a0[t] = pr[kR - 1];
-            m.a2[t] = pb[kR - 1];
-            m.a1[t] = pr[0];
+            m.x.a2[t] = pb[kR - 1];
+            m.x.a1[t] = pr[0];
             a3[t] = pb[0];
             group_order();
             double pq = 0.0;
@@ -479,10 +300,10 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(2))) void r
                     const double* c = kw - 2 * n + 4 * lane;
                     ua0 = c[1];
                     ub0 = c[3];
-                    fa = 0.5 * (ua0 + west(c[2])) * (m.a2[t - 64] - pr[0]);
+                    fa = 0.5 * (ua0 + west(c[2])) * (m.x.a2[t - 64] - pr[0]);
                     fb = 0.5 * (ub0 + c[0]) * (a0[t - 64] - pb[0]);
                 }
-                const double upa = wv < kNT / 64 - 1 ? m.a1[t + 64] : 0.0, upb = wv < kNT / 64 - 1 ? a3[t + 64] : 0.0;
+                const double upa = wv < kNT / 64 - 1 ? m.x.a1[t + 64] : 0.0, upb = wv < kNT / 64 - 1 ? a3[t + 64] : 0.0;
                 double cell[kR][4];
                 auto load = [&](int k) {
                     const double* c = kw + k * (2 * n) + 4 * lane;

@@ -32,6 +32,7 @@
 #include "common.h"
 #include "lanes.h"
 #include "resident.h"
+#include "strips7.h"
 #include "walks.h"
 
 namespace mls {
@@ -129,6 +130,7 @@ struct Map {
     int fine_n;
     double* cinv;  // 9 x 9 inverse of the h = 1/4 operator (LDS or the slot), FP64 only
     T* ring;       // LDS rows of the fused row walks (null: the walks are off)
+    Levels5<T>* low;  // LDS levels of the h = 1/128 visit in registers (kVisit7)
 };
 
 __host__ __device__ inline int64_t lds_coarse_elems(int top)
@@ -177,6 +179,7 @@ __device__ inline Map<T> make_map(T* slot, T* lds, int l, int64_t lds_budget_ele
     M.l = l;
     M.cinv = cinv;
     M.ring = ring;
+    M.low = reinterpret_cast<Levels5<T>*>(lds);
     lds_policy(l, sizeof(T) == 8, lds ? lds_budget_elems : 0, &M.lds_top, &M.fine_n);
     return M;
 }
@@ -661,6 +664,112 @@ __device__ double vcycle(const Map<T>& M, const Lv<T, W>& F, const T* __restrict
     return up_step<BS>(F, coarse_level(M, l - 1), rhs, sol, nu, want_dot, red);
 }
 
+// Walking workgroups of 1024 threads visit h = 1/128 with its nodes in
+// registers (cycle7): with separate passes that level and those below it took
+// a quarter of an iteration at h = 1/256, most of it latency (256 particles,
+// us a visit: FP64 144 -> 76, mixed 116 -> 27; 1024 particles at h = 1/256
+// 35.1 -> 32.0 ms, mixed 30.5 -> 24.3).  Its slot keeps
+// the edges; what its coefficients took holds, per wave, the inverse
+// diagonals (layout of resident7.hip) and the h = 1/64 weights, the LDS the
+// levels below, and the exchange between strips uses the walks' ring, which
+// every walk clears first.
+template <int BS, int WK>
+constexpr bool kVisit7 = BS == 1024 && WK == 2;
+constexpr int kWave7 = 2 * kRows7<1024> * 64 + kW * (kRows7<1024> / 4) * 64;
+static_assert(16 * kWave7 <= 2 * 128 * 128, "fits in the level's coefficients");
+
+// (A function of its own, and the mixed form's visit too: inlined, they cost
+// the kernel around them more registers than a call.  FP64, 1024 particles at
+// h = 1/256 / 256 at 1/512: set-up called 32.0 / 34.3 ms, inlined 32.3 / 34.5,
+// visit called too 33.6 / 35.5; mixed: both called 24.3 / 30.5, both inlined
+// 33.4 / 38.7.)
+template <typename T>
+__device__ __noinline__ void setup7(const Map<T>& M)
+{
+    constexpr int R = kRows7<1024>;
+    const Lv<T> C = coarse_level(M, 7);
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    T* mine = C.kap + wv * kWave7;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int j = R * wv + k, c = j * C.s + 2 * lane;
+        T ia = T(0), ib = T(0);
+        if (j > 0) {
+            const T in = C.wx[c], da = lane > 0 ? C.wx[c - 1] + in + C.wy[c - C.s] + C.wy[c] : T(0);
+            const T db = in + C.wx[c + 1] + C.wy[c + 1 - C.s] + C.wy[c + 1];
+            ia = lane > 0 ? T(1) / da : T(0);
+            ib = T(1) / db;
+        }
+        T* d = mine + (k >> 1) * 256 + (k & 1) + 2 * lane;
+        d[0] = k & 1 ? ib : ia;    // the red node's
+        d[128] = k & 1 ? ia : ib;  // the black node's
+    }
+    weights6<T, 1024>(mine + 2 * R * 64, coarse_level(M, 6).kap, t);
+    build_levels5(*M.low, coarse_level(M, 5).kap, t);
+    __syncthreads();
+    clear_levels5<T, 1024>(*M.low, t);
+    __syncthreads();
+}
+
+template <typename T>
+__device__ __forceinline__ void visit7_here(const Lv<T>& C, T* ring, Levels5<T>* low)
+{
+    constexpr int R = kRows7<1024>;
+    const int t0 = threadIdx.x, s = C.s;
+    const int wv = __builtin_amdgcn_readfirstlane(t0 >> 6);
+    const gmem<const T> wx = (gmem<const T>)(C.wx + R * wv * s), wy = (gmem<const T>)(C.wy + R * wv * s);
+    const gmem<const T> gb = (gmem<const T>)(C.b + R * wv * s);
+    const gmem<T> gx = (gmem<T>)(C.x + R * wv * s);
+    const T* mine = C.kap + wv * kWave7;
+    const gmem<const T> gi = (gmem<const T>)mine;
+    T rr[R], rb[R], zr[R], zb[R];
+    {
+        const int lane = again(t0) & 63;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {  // the boundary's entries may hold anything
+            const bool in = wv > 0 || k > 0;
+            const T a = gb[k * s + 2 * lane], b = gb[k * s + 2 * lane + 1];
+            const T va = in && lane > 0 ? a : T(0), vb = in ? b : T(0);
+            rr[k] = k & 1 ? vb : va;
+            rb[k] = k & 1 ? va : vb;
+        }
+    }
+    struct Edges { T x, y, z, w; };
+    auto edge = [&](int k, int u) -> Edges {
+        const int c = k * s + 2 * (u & 63);
+        return {wx[c], wx[c + 1], wy[c], wy[c + 1]};
+    };
+    auto inv = [&](int k, int c, int u) -> T { return gi[(k >> 1) * 256 + c * 128 + (k & 1) + 2 * (u & 63)]; };
+    cycle7<T, 1024>(rr, rb, zr, zb, edge, inv, mine + 2 * R * 64, *reinterpret_cast<Exchange7<T, 1024>*>(ring),
+                    *low, t0, wv);
+    const int lane = again(t0) & 63;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {  // zero on the boundary
+        gx[k * s + 2 * lane] = k & 1 ? zb[k] : zr[k];
+        gx[k * s + 2 * lane + 1] = k & 1 ? zr[k] : zb[k];
+    }
+    __syncthreads();
+}
+// ring, low: LDS addresses (a generic pointer's accesses would be flat ones)
+template <typename T>
+__device__ __noinline__ void visit7_call(T* wx, T* wy, T* x, T* b, T* kap, unsigned ring, unsigned low)
+{
+    Lv<T> C;
+    C.wx = wx; C.wy = wy; C.x = x; C.b = b; C.kap = kap;
+    C.n = 128; C.lg = 7; C.s = 129;
+    visit7_here(C, (T*)(lmem<T>)ring, (Levels5<T>*)(lmem<Levels5<T>>)low);
+}
+template <typename T>
+__device__ __forceinline__ void visit7(const Map<T>& M)
+{
+    const Lv<T> C = coarse_level(M, 7);
+    if constexpr (sizeof(T) == 8)
+        visit7_here(C, M.ring, M.low);
+    else
+        visit7_call<T>(C.wx, C.wy, C.x, C.b, C.kap, (unsigned)(uintptr_t)(lmem<T>)M.ring,
+                       (unsigned)(uintptr_t)(lmem<Levels5<T>>)M.low);
+}
+
 // The V(1,1) cycle with the fused row walks on every level that has them
 // (walk_down / walk_up); the smaller levels keep the separate sweeps.  With
 // Q the finest down walk first updates rhs -= alpha Q (and X += alpha Pn).
@@ -701,9 +810,38 @@ __device__ double vcycle_walk(const Map<T>& M, const Lv<T, W>& F, T* rhs, const 
     const Lv<T> C = coarse_level(M, l - 1);
     return walk_up<BS, true, false>(F, C.x, C.s, rhs, sol, want_dot, M.ring, red);
 }
+// the same with walks down to h = 1/256 and the h = 1/128 visit in registers
+template <int BS, typename T, typename W>
+__device__ __forceinline__ double vcycle_walk7(const Map<T>& M, const Lv<T, W>& F, T* rhs, const T* Q, T alpha,
+                                               T* X, const T* Pn, T* sol, bool want_dot, double* red)
+{
+    const int l = M.l;
+    walk_down_here<BS, true, false>(F, coarse_level(M, l - 1), rhs, Q, alpha, X, Pn, M.ring);
+    for (int Lk = l - 1; Lk > 7; --Lk) {
+        const Lv<T> L = coarse_level(M, Lk);
+        walk_down_here<BS, false, false>(L, coarse_level(M, Lk - 1), L.b, (const T*)nullptr, T(0), (T*)nullptr,
+                                         (const T*)nullptr, M.ring);
+    }
+    visit7(M);
+    for (int Lk = 8; Lk <= l - 1; ++Lk) {
+        const Lv<T> L = coarse_level(M, Lk);
+        const Lv<T> C = coarse_level(M, Lk - 1);
+        walk_up_here<BS, false, false>(L, C.x, C.s, L.b, L.x, false, M.ring, red);
+    }
+    const Lv<T> C = coarse_level(M, l - 1);
+    return walk_up_here<BS, true, false>(F, C.x, C.s, rhs, sol, want_dot, M.ring, red);
+}
+template <int BS, int WK, typename T, typename W>
+__device__ __forceinline__ double walked_cycle(const Map<T>& M, const Lv<T, W>& F, T* rhs, const T* Q, T alpha,
+                                               T* X, const T* Pn, T* sol, bool want_dot, double* red)
+{
+    if constexpr (kVisit7<BS, WK>) return vcycle_walk7<BS>(M, F, rhs, Q, alpha, X, Pn, sol, want_dot, red);
+    else return vcycle_walk<BS>(M, F, rhs, Q, alpha, X, Pn, sol, want_dot, red);
+}
 
 // ------------------------------------------------------- setup & obs --
-template <int BS, typename T, typename KT>
+// V7: the levels below h = 1/128 as visit7 wants them
+template <int BS, bool V7, typename T, typename KT>
 __device__ void setup_hierarchy(const Map<T>& M, const Lv<T>& F, const KT* __restrict__ kap,
                                 float* wx32 = nullptr, float* wy32 = nullptr)
 {
@@ -713,14 +851,18 @@ __device__ void setup_hierarchy(const Map<T>& M, const Lv<T>& F, const KT* __res
         Lv<T> C = coarse_level(M, l - 1);
         coarsen_kappa<BS>(kap, C.kap, l - 1);
         __syncthreads();
-        for (int L = l - 1; L >= 1; --L) {
+        constexpr int Lc = V7 ? 5 : 1;
+        for (int L = l - 1; L >= Lc; --L) {
             Lv<T> V = coarse_level(M, L);
-            edge_weights<BS>(V.kap, V.wx, V.wy, V.n, V.lg);
-            zero_boundary<BS>(V.x, V.n);
-            if (L >= 2) coarsen_kappa<BS>(V.kap, coarse_level(M, L - 1).kap, L - 1);
+            if (!V7 || L >= 7) {
+                edge_weights<BS>(V.kap, V.wx, V.wy, V.n, V.lg);
+                zero_boundary<BS>(V.x, V.n);
+            }
+            if (L > Lc) coarsen_kappa<BS>(V.kap, coarse_level(M, L - 1).kap, L - 1);
             __syncthreads();
         }
         __syncthreads();
+        if constexpr (V7) setup7(M);
     }
 }
 
@@ -810,7 +952,7 @@ __device__ inline Lv<T> fine_level(const Map<T>& M)
 
 // ---------------------------------------------------------- FP64 solve --
 template <int BS, int WK, bool KEEP_X>
-__device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& C, double* red)
+__device__ __forceinline__ void solve_one_f64_here(const Map<double>& M, const Job& J, const Common& C, double* red)
 {
     const int l = J.l;
     double *X = fine_array(M, FX), *R = fine_array(M, FR), *Z = fine_array(M, FZ), *Q = fine_array(M, FQ);
@@ -831,9 +973,9 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
     zero_boundary<BS>(Z, F.n);
     zero_boundary<BS>(Pb[0], F.n);
     zero_boundary<BS>(Pb[1], F.n);
-    setup_hierarchy<BS>(M, F, kap, FV.wx, FV.wy);
+    setup_hierarchy<BS, kVisit7<BS, WK>>(M, F, kap, FV.wx, FV.wy);
     if (l == 2) build_coarse_inverse<BS>(FV, M.cinv);
-    else if (l >= 3) build_coarse_inverse<BS>(coarse_level(M, 2), M.cinv);
+    else if (l >= 3 && !kVisit7<BS, WK>) build_coarse_inverse<BS>(coarse_level(M, 2), M.cinv);
     // The forward map needs the solution only at the observation points
     // unless the whole field is asked for (p_out; KEEP_X).  G = Obs x is
     // linear in x = sum_k alpha_k p_k, so without p_out each step adds
@@ -849,7 +991,7 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
         for (int o = threadIdx.x; o < C.nobs; o += BS) J.G[o] = 0.0;
     __syncthreads();
     if (walks) {
-        vcycle_walk<BS>(M, FV, R, (const double*)nullptr, 0.0, (double*)nullptr, (const double*)nullptr, Z,
+        walked_cycle<BS, WK>(M, FV, R, (const double*)nullptr, 0.0, (double*)nullptr, (const double*)nullptr, Z,
                         false, red);
     } else {
         vcycle<BS>(M, FV, R, Z, C.nu, false, false, red);
@@ -899,7 +1041,7 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
         if (!keep_x) observe_step<BS>(J, C, Pn, alpha);
         double rzn;
         if (walks) {  // the r update rides on the down walk
-            rzn = vcycle_walk<BS>(M, FV, R, Q, alpha, (double*)nullptr, (const double*)nullptr, Z, true, red);
+            rzn = walked_cycle<BS, WK>(M, FV, R, Q, alpha, (double*)nullptr, (const double*)nullptr, Z, true, red);
         } else {
             // the r update fused with the first red sweep of the V-cycle
             MLS_FOR_INTERIOR(F, {
@@ -924,6 +1066,12 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
     observe_and_store<BS, keep_x>(J, C, X, F.n, st, it, red);
 }
 
+template <int BS, int WK, bool KEEP_X>
+__device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& C, double* red)
+{
+    solve_one_f64_here<BS, WK, KEEP_X>(M, J, C, red);
+}
+
 // --------------------------------------------------------- mixed solve --
 // FP32 multigrid-PCG with residual replacement in FP64: the system matrix is
 // the one defined by the FP32 edge weights (promoted exactly to FP64 for the
@@ -940,7 +1088,7 @@ __device__ void solve_one_f64(const Map<double>& M, const Job& J, const Common& 
 constexpr double kDrift2 = 1e-6;  // replace r after (r, z) fell by this factor (1e-3 in norm)
 
 template <int BS, int WK>
-__device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common& C, double* red)
+__device__ __forceinline__ void solve_one_mixed_here(const Map<float>& M, const Job& J, const Common& C, double* red)
 {
     const int l = J.l;
     float *X = fine_array(M, FX), *R = fine_array(M, FR), *Z = fine_array(M, FZ), *Q = fine_array(M, FQ);
@@ -957,7 +1105,7 @@ __device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common&
     zero_boundary<BS>(Pb[0], F.n);
     zero_boundary<BS>(Pb[1], F.n);
     zero_boundary<BS>(X64, F.n);
-    setup_hierarchy<BS>(M, F, kap);
+    setup_hierarchy<BS, kVisit7<BS, WK>>(M, F, kap);
     MLS_FOR_INTERIOR(F, { X64[c] = 0.0; X[c] = 0.f; R[c] = (float)h2; })
     __syncthreads();
     // x64 += x32, x32 = 0, then r = b - A x64 in FP64 (rounded to FP32)
@@ -977,7 +1125,7 @@ __device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common&
     };
     auto precondition = [&]() {  // z = V r and (r, z)
         if (walks) {
-            return vcycle_walk<BS>(M, F, R, (const float*)nullptr, 0.f, (float*)nullptr, (const float*)nullptr, Z,
+            return walked_cycle<BS, WK>(M, F, R, (const float*)nullptr, 0.f, (float*)nullptr, (const float*)nullptr, Z,
                                    true, red);
         }
         vcycle<BS>(M, F, R, Z, C.nu, false, false, red);
@@ -1016,7 +1164,7 @@ __device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common&
         const float alpha = (float)(rz / pq);
         double rzn;
         if (walks) {  // the x and r updates ride on the down walk
-            rzn = vcycle_walk<BS>(M, F, R, Q, alpha, X, Pn, Z, true, red);
+            rzn = walked_cycle<BS, WK>(M, F, R, Q, alpha, X, Pn, Z, true, red);
         } else {
             MLS_FOR_INTERIOR(F, {
                 X[c] += alpha * Pn[c];
@@ -1054,6 +1202,11 @@ __device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common&
         __syncthreads();
     }
     observe_and_store<BS>(J, C, X64, F.n, st, it, red);
+}
+template <int BS, int WK>
+__device__ void solve_one_mixed(const Map<float>& M, const Job& J, const Common& C, double* red)
+{
+    solve_one_mixed_here<BS, WK>(M, J, C, red);
 }
 
 // ----------------------------------------------------- single-level kernel --
@@ -1127,13 +1280,17 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_kernel(SolveParams P
         J.obs_w = P.obs_w;
         if (MIXED) {
             float* ring = (WK == 2 && P.ring_off >= 0) ? (float*)mls_lds + P.ring_off : nullptr;
-            solve_one_mixed<BS, WK>(make_map((float*)P.ws + (int64_t)blockIdx.x * P.slot_elems, (float*)mls_lds, l,
-                                         P.lds_elems, nullptr, ring), J, P.C, red);
+            const Map<float> M = make_map((float*)P.ws + (int64_t)blockIdx.x * P.slot_elems, (float*)mls_lds, l,
+                                          P.lds_elems, nullptr, ring);
+            if constexpr (kVisit7<BS, WK>) solve_one_mixed_here<BS, WK>(M, J, P.C, red);
+            else solve_one_mixed<BS, WK>(M, J, P.C, red);
         } else {
             double* slot = (double*)P.ws + (int64_t)blockIdx.x * P.slot_elems;
             double* cinv = P.cinv_lds ? (double*)mls_lds + P.lds_elems : slot + hier_elems(l, false);
             double* ring = (WK == 2 && P.ring_off >= 0) ? (double*)mls_lds + P.ring_off : nullptr;
-            solve_one_f64<BS, WK, PX>(make_map(slot, (double*)mls_lds, l, P.lds_elems, cinv, ring), J, P.C, red);
+            const Map<double> M = make_map(slot, (double*)mls_lds, l, P.lds_elems, cinv, ring);
+            if constexpr (kVisit7<BS, WK>) solve_one_f64_here<BS, WK, PX>(M, J, P.C, red);
+            else solve_one_f64<BS, WK, PX>(M, J, P.C, red);
         }
     }
     // every workgroup has drawn past the end; the last one to finish resets
@@ -1207,11 +1364,15 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_list_kernel(ListPara
         T* slot = (T*)P.ws + (int64_t)blockIdx.x * P.slot_elems;
         T* ring = WK == 2 ? (T*)mls_lds + P.ring_off : nullptr;
         if constexpr (MIXED) {
-            solve_one_mixed<BS, WK>(make_map(slot, (T*)mls_lds, l, P.lds_elems, nullptr, ring), J, P.C, red);
+            const Map<T> M = make_map(slot, (T*)mls_lds, l, P.lds_elems, nullptr, ring);
+            if constexpr (kVisit7<BS, WK>) solve_one_mixed_here<BS, WK>(M, J, P.C, red);
+            else solve_one_mixed<BS, WK>(M, J, P.C, red);
         } else {
             double* cinv = P.cinv_lds ? (double*)mls_lds + P.lds_elems : slot + hier_elems(l, false);
-            solve_one_f64<BS, WK, false>(make_map(slot, (T*)mls_lds, l, P.lds_elems, cinv, ring), J, P.C,
-                                         red);  // work items carry no p_out
+            // work items carry no p_out
+            const Map<T> M = make_map(slot, (T*)mls_lds, l, P.lds_elems, cinv, ring);
+            if constexpr (kVisit7<BS, WK>) solve_one_f64_here<BS, WK, false>(M, J, P.C, red);
+            else solve_one_f64<BS, WK, false>(M, J, P.C, red);
         }
     }
     // as in solve_kernel: the last workgroup to finish resets the counter
@@ -1306,6 +1467,12 @@ static size_t lds_bytes_for(const mls2mc_ctx* ctx, int l, bool mixed, int bs, bo
     // the row walks' rows come first: the residency gets what is left
     const int64_t ring = walks ? walk_ring_elems(bs, l) : 0;
     const int64_t ring_bytes = ring * (int64_t)esz;
+    if (walks && bs == 1024) {  // kVisit7: the levels below h = 1/64 instead of any residency
+        *alloc_elems = 0;
+        *cinv_lds = 0;
+        *ring_off = (int64_t)((mixed ? sizeof(Levels5<float>) : sizeof(Levels5<double>)) / esz);
+        return (size_t)(*ring_off + ring) * esz;
+    }
     const int64_t cinv_bytes = mixed ? 0 : kCinvElems * 8;
     if (walks && budget > ctx->max_lds - ring_bytes - cinv_bytes)
         budget = std::max<int64_t>(0, ctx->max_lds - ring_bytes - cinv_bytes);
@@ -1573,17 +1740,12 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
         ListChunk lc;
         lc.n = (int)ch.size();
         lc.tiles = 0;
-        // Particles of h = 1/256 and finer that fill the device get a launch
-        // of their own, with the fused row walks; fewer share the next launch
-        // with the smaller levels' particles, which fill the other CUs.
-        int64_t big = 0;
-        bool walks = true;
+        // Particles of h = 1/256 and finer get a launch of their own, with the
+        // fused row walks, so a batch solves them as single forwards do.
+        bool split = true;
         for (const Piece& pc : ch)
-            if (pc.it.l >= 8) {
-                big += pc.it.N;
-                walks = walks && launch_walks(pc.it.l, list_block(ctx, pc.it.l), make_common(ctx, pc.it.l).nu);
-            }
-        const bool split = walks && big >= ctx->n_cu;
+            if (pc.it.l >= 8)
+                split = split && launch_walks(pc.it.l, list_block(ctx, pc.it.l), make_common(ctx, pc.it.l).nu);
         size_t kap_off = 0;
         for (size_t i = 0; i < ch.size(); ++i) {
             const FwdItem& it = ch[i].it;

@@ -129,7 +129,7 @@ __device__ __forceinline__ void lds_barrier()
 // coarse_red (flow cell): C.x gets the coarse level's first red sweep from
 // zero too, for a coarser level with separate sweeps.
 template <int BS, bool FINE, bool FLOW, typename T, typename LEVEL, typename COARSE>
-__device__ void walk_down(const LEVEL& L, const COARSE& C, T* __restrict__ b, const T* __restrict__ Q, T alpha,
+__device__ __forceinline__ void walk_down_here(const LEVEL& L, const COARSE& C, T* __restrict__ b, const T* __restrict__ Q, T alpha,
                           T* __restrict__ X, const T* __restrict__ Pn, T* __restrict__ ring, bool coarse_red = false)
 {
     using W = std::remove_const_t<std::remove_reference_t<decltype(*L.wx)>>;
@@ -281,7 +281,7 @@ __device__ void walk_down(const LEVEL& L, const COARSE& C, T* __restrict__ b, co
 // pass through the LDS ring as in walk_down.  The walk reads only what no
 // band writes during it (the right-hand side, the weights, the correction).
 template <int BS, bool FINE, bool FLOW, typename T, typename LEVEL>
-__device__ double walk_up(const LEVEL& L, const T* __restrict__ e, int sc, const T* __restrict__ b,
+__device__ __forceinline__ double walk_up_here(const LEVEL& L, const T* __restrict__ e, int sc, const T* __restrict__ b,
                           T* __restrict__ x, bool want_dot, T* __restrict__ ring, double* red)
 {
     using W = std::remove_const_t<std::remove_reference_t<decltype(*L.wx)>>;
@@ -407,6 +407,22 @@ __device__ double walk_up(const LEVEL& L, const T* __restrict__ e, int sc, const
     }
     __syncthreads();  // the new z is complete
     return want_dot ? block_sum<BS>(dot, red) : 0.0;
+}
+
+// The compiler's choice of a call or not (the ..._here forms are always inlined:
+// the 1024-thread solver needs that, forced everywhere it cost the 512-thread
+// mixed form 482 -> 616 ms per 4096 particles at h = 1/512).
+template <int BS, bool FINE, bool FLOW, typename T, typename LEVEL, typename COARSE>
+__device__ void walk_down(const LEVEL& L, const COARSE& C, T* __restrict__ b, const T* __restrict__ Q, T alpha,
+                          T* __restrict__ X, const T* __restrict__ Pn, T* __restrict__ ring, bool coarse_red = false)
+{
+    walk_down_here<BS, FINE, FLOW>(L, C, b, Q, alpha, X, Pn, ring, coarse_red);
+}
+template <int BS, bool FINE, bool FLOW, typename T, typename LEVEL>
+__device__ double walk_up(const LEVEL& L, const T* __restrict__ e, int sc, const T* __restrict__ b,
+                          T* __restrict__ x, bool want_dot, T* __restrict__ ring, double* red)
+{
+    return walk_up_here<BS, FINE, FLOW>(L, e, sc, b, x, want_dot, ring, red);
 }
 
 }  // namespace mls
