@@ -531,8 +531,10 @@ int mls2mc_autotune(mls2mc_ctx* ctx, int l, int64_t N, double* best_ms, void* st
  * schedules cached by the caller.  With everything default (nu 1 counts as
  * default), or everything but the block and that one the level's default
  * block, levels h = 1/8 .. 1/64 run the register-resident solver, which has
- * launch shapes of its own; the autotuner tries it first and returns it as
- * {0, default block, 0, 0}.                                                */
+ * launch shapes of its own, and so does h = 1/128 of the FP64 Dirichlet
+ * problem with at most 128 observations, in launches that do not return the
+ * field; the autotuner tries it first and returns it as {0, default block,
+ * 0, 0}.                                                                   */
 int mls2mc_get_launch(const mls2mc_ctx* ctx, int l, int* grid, int* block, int* nu, int* lds_bytes);
 int mls2mc_set_launch(mls2mc_ctx* ctx, int l, int grid, int block, int nu, int lds_bytes);
 

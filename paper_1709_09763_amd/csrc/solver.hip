@@ -1389,10 +1389,10 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_list_kernel(ListPara
 // From h = 1/128 on one workgroup of 1024 threads per CU: the particle's
 // passes stream from memory, and sixteen waves on one particle keep more
 // loads in flight than two particles' eight, over half the slots' footprint
-// (us per 512 solves, 512 threads at four workgroups per CU -> 1024 at one:
-// FP64 h = 1/128 6627 -> 5427, 1/256 26640 -> 20344, 1/512 101173 -> 78620;
-// mixed 4090 -> 3723, 17288 -> 17049, 77095 -> 74386; 64 solves at h = 1/512
-// 42.8 -> 30.6 ms).
+// (ms, 512 threads at two workgroups per CU -> 1024 at one, 1024 solves: FP64
+// h = 1/256 41.5 -> 32.2, 1/512 159.5 -> 130.9; mixed 34.2 -> 24.3, 134.7 ->
+// 109.3; 512 solves at h = 1/128 outside the resident solver, 512 threads at
+// four per CU: FP64 6.63 -> 5.43, mixed 4.09 -> 3.72).
 static int default_block(int l)
 {
     if (l <= 4) return 64;
@@ -1404,8 +1404,9 @@ static int default_block(int l)
 // LDS budget of level l in bytes.  The library's own choice beside the
 // default block: FP64 at h = 1/128 takes all there is (the fine level's FP32
 // weights of the V-cycle then fit: 5.43 ms per 512 solves against 5.78 at
-// 64 KiB), the mixed form none from h = 1/128 on (3.72 ms against 4.07; the
-// coarse levels' flat accesses cost more than L2 hits), else 64 KiB.
+// 64 KiB), the mixed form none there (3.72 ms against 4.07; the coarse levels'
+// flat accesses cost more than L2 hits), else 64 KiB.  The row walks of 1024
+// threads take no residency (lds_bytes_for).
 static int64_t lds_budget(const mls2mc_ctx* ctx, int l, bool mixed)
 {
     int64_t budget = ctx->solver_lds[l];
