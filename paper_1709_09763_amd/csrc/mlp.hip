@@ -224,10 +224,10 @@ struct Surrogate {
     float *X = nullptr, *Z1 = nullptr, *H1 = nullptr, *Z2 = nullptr, *H2 = nullptr, *OUT = nullptr;
     float *T = nullptr, *D3 = nullptr, *D2 = nullptr, *D1 = nullptr, *loss = nullptr;
     int32_t* perm = nullptr;
-    // fused path: BF16 copies of the weights as MFMA operands, and the
-    // transposed batch for the weight gradients (see MlpDims)
+    // fused path: BF16 copies of the weights as MFMA operands (null: the
+    // layer-by-layer products), and the transposed batch for the weight
+    // gradients (see MlpDims)
     __bf16* w16 = nullptr;
-    bool w16_fresh = false;  // the copies are those of p
     char* tr = nullptr;
     int64_t tr_rows = 0;
     double* lossp = nullptr;
@@ -310,10 +310,12 @@ static int sur_backward(Surrogate* S, int64_t B, hipStream_t s)
 // rows through standardisation, the three layers, the loss and the two
 // backward products with the activations in LDS, and a second one (9 us)
 // forms all weight gradients and applies Adam in their epilogue.
-// Weights are read as BF16 copies (kept by the Adam epilogue; rounding the
-// FP32 master as the fragments were loaded before gives the same operands)
-// and the batch is handed over transposed, so every fragment is one or two
-// 16-byte loads.  The MFMA tiles, their k order and the FP32 epilogues are
+// Weights are read as BF16 copies (rounding the FP32 master as the fragments
+// were loaded before gives the same operands), which every call that changes
+// the parameters brings in line on its own stream: the initialisation, new
+// parameters, the Adam epilogue.  A call that only reads them never has to, so
+// a captured one replays with the parameters of the day.  The batch is handed
+// over transposed, so every fragment is one or two 16-byte loads.  The MFMA tiles, their k order and the FP32 epilogues are
 // those of mlp_gemm, so the parameters are bitwise the same.
 struct MlpDims {
     int D, H, O;     // inputs, hidden width (a multiple of 16), outputs
@@ -620,16 +622,12 @@ __global__ __launch_bounds__(256) void loss_sum_kernel(int n, const double* __re
 // the layer-by-layer products.
 static bool mlp_fits(const mls2mc_ctx* ctx) { return mlp_dims(ctx->sur).lds() <= (size_t)ctx->max_lds; }
 
-// the BF16 copies, made anew when the parameters changed outside training
-static int mlp_refresh(Surrogate* S, hipStream_t s)
+// the BF16 copies of the parameters, made anew (a network of the layer-by-layer
+// products has none)
+static int mlp_copies(const Surrogate* S, hipStream_t s)
 {
+    if (!S->w16) return MLS2MC_OK;
     const MlpDims d = mlp_dims(S);
-    if (!S->w16) {
-        MLS_CHECK_HIP(hipMalloc(&S->w16, sizeof(__bf16) * (size_t)d.total()));
-        zero16_kernel<<<(unsigned)((d.total() + 255) / 256), 256, 0, s>>>(d.total(), S->w16);
-        S->w16_fresh = false;
-    }
-    if (S->w16_fresh) return MLS2MC_OK;
     auto copy = [&](int M, int N, const float* w, int64_t c, int ldc, int64_t ct, int ldt) {
         mlp_copy_kernel<<<(unsigned)(((int64_t)M * N + 255) / 256), 256, 0, s>>>(M, N, w, S->w16 + c, ldc,
                                                                                 ct >= 0 ? S->w16 + ct : nullptr, ldt);
@@ -638,7 +636,6 @@ static int mlp_refresh(Surrogate* S, hipStream_t s)
     copy(d.H, d.H, S->W2(), d.w2(), d.Hp, d.w2t(), d.Hp);
     copy(d.O, d.H, S->W3(), d.w3(), d.Hp, d.w3t(), d.Op);
     MLS_CHECK_HIP(hipGetLastError());
-    S->w16_fresh = true;
     return MLS2MC_OK;
 }
 
@@ -901,6 +898,12 @@ int mls2mc_surrogate_init(mls2mc_ctx* ctx, int hidden, int64_t capacity, uint64_
                                                                          std::sqrt(2.0f / L[q].fan), L[q].w);
         MLS_CHECK_HIP(hipGetLastError());
     }
+    if (mlp_fits(ctx)) {  // the padding of the copies stays zero
+        const int64_t n16 = mlp_dims(S).total();
+        MLS_CHECK_HIP(hipMalloc(&S->w16, sizeof(__bf16) * (size_t)n16));
+        zero16_kernel<<<(unsigned)((n16 + 255) / 256), 256, 0, s>>>(n16, S->w16);
+        MLS_TRY(mlp_copies(S, s));
+    }
     MLS_CHECK_HIP(hipStreamSynchronize(s));
     z.release();
     return MLS2MC_OK;
@@ -914,10 +917,9 @@ int mls2mc_surrogate_n_params(const mls2mc_ctx* ctx)
 int mls2mc_surrogate_set_params(mls2mc_ctx* ctx, const float* params, void* stream)
 {
     MLS_REQUIRE(ctx && ctx->sur && params, "surrogate_set_params: no surrogate or null pointer");
-    ctx->sur->w16_fresh = false;
     MLS_CHECK_HIP(hipMemcpyAsync(ctx->sur->p, params, sizeof(float) * ctx->sur->np, hipMemcpyDeviceToDevice,
                                  (hipStream_t)stream));
-    return MLS2MC_OK;
+    return mlp_copies(ctx->sur, (hipStream_t)stream);
 }
 
 int mls2mc_surrogate_get_params(mls2mc_ctx* ctx, float* params, void* stream)
@@ -965,9 +967,8 @@ int mls2mc_surrogate_train(mls2mc_ctx* ctx, int epochs, int batch, double lr, ui
     MLS_REQUIRE(epochs >= 0 && batch >= 1 && batch <= 65536 && lr > 0, "surrogate_train: bad epochs/batch/lr");
     MLS_REQUIRE(S->count >= batch, "surrogate_train: fewer pairs than one batch");
     const hipStream_t s = (hipStream_t)stream;
-    const bool fused = mlp_fits(ctx);
-    if (fused) MLS_TRY(mlp_refresh(S, s));
-    else MLS_TRY(sur_ensure_batch(S, batch));
+    const bool fused = S->w16 != nullptr;
+    if (!fused) MLS_TRY(sur_ensure_batch(S, batch));
     const int64_t n = S->count;
     // standardisation statistics of the current dataset
     col_stats_kernel<<<S->D, 256, 0, s>>>(n, S->D, S->ds_th, S->mu_x, S->sd_x);
@@ -1001,7 +1002,6 @@ int mls2mc_surrogate_train(mls2mc_ctx* ctx, int epochs, int batch, double lr, ui
                 adam_kernel<<<(unsigned)((S->np + 255) / 256), 256, 0, s>>>(S->np, S->p, S->g, S->m, S->v, (float)lr,
                                                                             b1, b2, c1, c2, eps);
                 MLS_CHECK_HIP(hipGetLastError());
-                S->w16_fresh = false;
             }
             if (bi == nb - 1 && loss_out) {
                 float l;
@@ -1025,9 +1025,8 @@ int mls2mc_surrogate_predict(mls2mc_ctx* ctx, int64_t N, const double* theta, do
         return launch_linear_map(N, ctx->prob.K, ctx->nobs, ctx->d_sur_S, theta, G_out, (hipStream_t)stream);
     Surrogate* S = ctx->sur;
     const hipStream_t s = (hipStream_t)stream;
-    if (mlp_fits(ctx)) {
+    if (S->w16) {
         MLS_REQUIRE((N + 15) / 16 < (int64_t(1) << 31), "surrogate_predict: N too large for one launch");
-        MLS_TRY(mlp_refresh(S, s));
         MlpRows P = mlp_rows(S, N);
         P.th = theta;
         P.out = G_out;
@@ -1064,8 +1063,7 @@ int mls2mc_surrogate_loss_grad(mls2mc_ctx* ctx, int64_t B, const double* x, cons
     MLS_REQUIRE(x && target && loss_out && grad_out, "surrogate_loss_grad: null pointer");
     Surrogate* S = ctx->sur;
     const hipStream_t s = (hipStream_t)stream;
-    if (mlp_fits(ctx)) {
-        MLS_TRY(mlp_refresh(S, s));
+    if (S->w16) {
         MLS_TRY(mlp_step(S, B, nullptr, x, target, false, false, 0.f, 0.f, 0.f, 1.f, 1.f, 0.f, s));
         MLS_TRY(mlp_loss(S, B, s));
     } else {
