@@ -57,6 +57,10 @@ struct DevBuf {
 };
 
 // ------------------------------------------------------------- sizes --
+// particles of one launch that gives each up to 512 threads: a grid holds less
+// than 2^32 threads
+constexpr int64_t kLaunchParticles = int64_t(1) << 22;
+
 inline int64_t n_side(int l) { return int64_t(1) << l; }
 inline int64_t n_elem(int l) { return 2 * n_side(l) * n_side(l); }
 inline int64_t n_unk(int l) { return (n_side(l) - 1) * (n_side(l) - 1); }

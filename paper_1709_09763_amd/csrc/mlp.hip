@@ -1026,13 +1026,15 @@ int mls2mc_surrogate_predict(mls2mc_ctx* ctx, int64_t N, const double* theta, do
     Surrogate* S = ctx->sur;
     const hipStream_t s = (hipStream_t)stream;
     if (S->w16) {
-        MLS_REQUIRE((N + 15) / 16 < (int64_t(1) << 31), "surrogate_predict: N too large for one launch");
-        MlpRows P = mlp_rows(S, N);
-        P.th = theta;
-        P.out = G_out;
-        if (S->standardized) { P.mux = S->mu_x; P.sdx = S->sd_x; P.muy = S->mu_y; P.sdy = S->sd_y; }
-        mlp_rows_kernel<false><<<(unsigned)((N + 15) / 16), kRowThreads, mlp_dims(S).lds(), s>>>(P);
-        MLS_CHECK_HIP(hipGetLastError());
+        for (int64_t q0 = 0; q0 < N; q0 += kLaunchParticles) {  // 64 threads a row
+            const int64_t B = std::min(kLaunchParticles, N - q0);
+            MlpRows P = mlp_rows(S, B);
+            P.th = theta + q0 * S->D;
+            P.out = G_out + q0 * S->O;
+            if (S->standardized) { P.mux = S->mu_x; P.sdx = S->sd_x; P.muy = S->mu_y; P.sdy = S->sd_y; }
+            mlp_rows_kernel<false><<<(unsigned)((B + 15) / 16), kRowThreads, mlp_dims(S).lds(), s>>>(P);
+            MLS_CHECK_HIP(hipGetLastError());
+        }
         return MLS2MC_OK;
     }
     const int64_t chunk = 4096;

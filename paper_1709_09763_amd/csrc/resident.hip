@@ -38,6 +38,7 @@
 // from z = 0 the red equations hold, so after the black sweep the red
 // residual is the sum of w z_black alone; A p is formed as the sum of
 // w (p_c - p_nb).
+#include <algorithm>
 #include <type_traits>
 
 #include "resident.h"
@@ -102,7 +103,7 @@ struct Mem {
 
 // ------------------------------------------------------------- kernel --
 struct ResParams {
-    int64_t N;
+    int64_t N, first;  // particles, and the first one of this launch
     const int64_t* N_dev;
     const void* kappa;
     double* G;
@@ -149,7 +150,7 @@ resident_kernel(ResParams A)
     } sm;
     M& m = sm.m;
 
-    int64_t q = blockIdx.x;
+    int64_t q = A.first + blockIdx.x;
     const void* kappa = A.kappa;
     double *Gq = A.G, *phi = A.phi;
     const double* y = A.y;
@@ -491,10 +492,13 @@ int launch_params(mls2mc_ctx* ctx, int l, int64_t total, bool mixed, ResParams& 
     A.inv_sigma = 1.0 / ctx->prob.sigma_n;
     A.tol2 = ctx->rtol * ctx->rtol;
     A.max_iters = ctx->max_iters;
-    MLS_REQUIRE(total < (int64_t(1) << 31), "solver: too many particles for one launch");
-    const unsigned grid = (unsigned)total;
-    if (ctx->prob.bc == MLS2MC_BC_FLOW_CELL) return launch_level<double, true>(l, grid, A, s);
-    return mixed ? launch_level<float, false>(l, grid, A, s) : launch_level<double, false>(l, grid, A, s);
+    for (A.first = 0; A.first < total; A.first += kLaunchParticles) {
+        const unsigned grid = (unsigned)std::min(kLaunchParticles, total - A.first);
+        if (ctx->prob.bc == MLS2MC_BC_FLOW_CELL) MLS_TRY((launch_level<double, true>(l, grid, A, s)));
+        else if (mixed) MLS_TRY((launch_level<float, false>(l, grid, A, s)));
+        else MLS_TRY((launch_level<double, false>(l, grid, A, s)));
+    }
+    return MLS2MC_OK;
 }
 
 }  // namespace

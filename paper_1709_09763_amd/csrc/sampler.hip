@@ -11,27 +11,31 @@
 namespace mls {
 
 // ------------------------------------------------------------ potential --
-// One wave per particle: its row is read by neighbouring lanes.
+// One wave per particle: its row is read by neighbouring lanes.  (The grid is
+// bounded, and the waves go on to further particles.)
+constexpr int64_t kWaveBlocks = int64_t(1) << 22;
+static unsigned wave_blocks(int64_t N) { return (unsigned)std::min<int64_t>((N + 3) / 4, kWaveBlocks); }
+
 __global__ __launch_bounds__(256) void loglik_kernel(int64_t N, int nobs, const double* __restrict__ G,
                                                      const double* __restrict__ y, double inv_sigma,
                                                      double* __restrict__ phi)
 {
-    const int64_t q = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
-    if (q >= N) return;
-    double s = 0.0;
-    for (int o = threadIdx.x & 63; o < nobs; o += 64) {
-        const double r = (y[o] - G[q * nobs + o]) * inv_sigma;
-        s += r * r;
+    for (int64_t q = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6); q < N; q += gridDim.x * (int64_t)4) {
+        double s = 0.0;
+        for (int o = threadIdx.x & 63; o < nobs; o += 64) {
+            const double r = (y[o] - G[q * nobs + o]) * inv_sigma;
+            s += r * r;
+        }
+        s = lane63_sum(s);
+        if ((threadIdx.x & 63) == 63) phi[q] = 0.5 * s;
     }
-    s = lane63_sum(s);
-    if ((threadIdx.x & 63) == 63) phi[q] = 0.5 * s;
 }
 
 int launch_loglik(mls2mc_ctx* ctx, int64_t N, const double* G, const double* y, double* phi,
                   hipStream_t s)
 {
     if (N == 0) return MLS2MC_OK;
-    loglik_kernel<<<(unsigned)((N + 3) / 4), 256, 0, s>>>(N, ctx->nobs, G, y, 1.0 / ctx->prob.sigma_n, phi);
+    loglik_kernel<<<wave_blocks(N), 256, 0, s>>>(N, ctx->nobs, G, y, 1.0 / ctx->prob.sigma_n, phi);
     MLS_CHECK_HIP(hipGetLastError());
     return MLS2MC_OK;
 }
@@ -810,45 +814,45 @@ __global__ __launch_bounds__(256) void pcn_accept_kernel(
     const int8_t* __restrict__ sth, double* __restrict__ th, double* __restrict__ Gl, double* __restrict__ Gh,
     double* __restrict__ pl, double* __restrict__ ph, uint8_t* __restrict__ acc)
 {
-    const int64_t j = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    if (j >= N) return;
     const bool need_lo = mode != 2, need_hi = mode != 0;
-    double psi_old, psi_new;
-    if (mode == 0) {
-        psi_old = beta * pl[j];
-        psi_new = beta * pln[j];
-    } else if (mode == 1) {
-        psi_old = beta * ((1.0 - zeta) * pl[j] + zeta * ph[j]);
-        psi_new = beta * ((1.0 - zeta) * pln[j] + zeta * phn[j]);
-    } else {
-        psi_old = beta * ph[j];
-        psi_new = beta * phn[j];
-    }
-    if (rwm) {
-        double qo = 0.0, qn = 0.0;
-        for (int k = lane; k < K; k += 64) {
-            qo += th[j * K + k] * th[j * K + k];
-            qn += thn[j * K + k] * thn[j * K + k];
+    for (int64_t j = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6); j < N; j += gridDim.x * (int64_t)4) {
+        double psi_old, psi_new;
+        if (mode == 0) {
+            psi_old = beta * pl[j];
+            psi_new = beta * pln[j];
+        } else if (mode == 1) {
+            psi_old = beta * ((1.0 - zeta) * pl[j] + zeta * ph[j]);
+            psi_new = beta * ((1.0 - zeta) * pln[j] + zeta * phn[j]);
+        } else {
+            psi_old = beta * ph[j];
+            psi_new = beta * phn[j];
         }
-        psi_old += 0.5 * wave_sum(qo);
-        psi_new += 0.5 * wave_sum(qn);
-    }
-    bool ok = true;
-    if (need_lo && stl && stl[j] != 0) ok = false;
-    if (need_hi && sth && sth[j] != 0) ok = false;
-    const bool a = ok && (log(u[j]) < -(psi_new - psi_old));
-    if (a) {
-        for (int k = lane; k < K; k += 64) th[j * K + k] = thn[j * K + k];
-        if (need_lo)
-            for (int o = lane; o < nobs; o += 64) Gl[j * nobs + o] = Gln[j * nobs + o];
-        if (need_hi)
-            for (int o = lane; o < nobs; o += 64) Gh[j * nobs + o] = Ghn[j * nobs + o];
-    }
-    if (lane == 0) {
-        if (a && need_lo) pl[j] = pln[j];
-        if (a && need_hi) ph[j] = phn[j];
-        if (acc) acc[j] = a ? 1 : 0;
+        if (rwm) {
+            double qo = 0.0, qn = 0.0;
+            for (int k = lane; k < K; k += 64) {
+                qo += th[j * K + k] * th[j * K + k];
+                qn += thn[j * K + k] * thn[j * K + k];
+            }
+            psi_old += 0.5 * wave_sum(qo);
+            psi_new += 0.5 * wave_sum(qn);
+        }
+        bool ok = true;
+        if (need_lo && stl && stl[j] != 0) ok = false;
+        if (need_hi && sth && sth[j] != 0) ok = false;
+        const bool a = ok && (log(u[j]) < -(psi_new - psi_old));
+        if (a) {
+            for (int k = lane; k < K; k += 64) th[j * K + k] = thn[j * K + k];
+            if (need_lo)
+                for (int o = lane; o < nobs; o += 64) Gl[j * nobs + o] = Gln[j * nobs + o];
+            if (need_hi)
+                for (int o = lane; o < nobs; o += 64) Gh[j * nobs + o] = Ghn[j * nobs + o];
+        }
+        if (lane == 0) {
+            if (a && need_lo) pl[j] = pln[j];
+            if (a && need_hi) ph[j] = phn[j];
+            if (acc) acc[j] = a ? 1 : 0;
+        }
     }
 }
 
@@ -859,7 +863,7 @@ int launch_pcn_accept(int64_t N, int K, int nobs, int mode, int rwm, double beta
                       double* Ghi, double* plo, double* phi, uint8_t* acc, hipStream_t s)
 {
     if (N == 0) return MLS2MC_OK;
-    pcn_accept_kernel<<<(unsigned)((N + 3) / 4), 256, 0, s>>>(
+    pcn_accept_kernel<<<wave_blocks(N), 256, 0, s>>>(
         N, K, nobs, mode, rwm, beta, zeta, u, th_new, Glo_new, Ghi_new, plo_new, phi_new, st_lo, st_hi,
         theta, Glo, Ghi, plo, phi, acc);
     MLS_CHECK_HIP(hipGetLastError());
