@@ -11,23 +11,44 @@
 namespace mls {
 
 // ------------------------------------------------------------ potential --
-// One wave per particle: its row is read by neighbouring lanes.  (The grid is
-// bounded, and the waves go on to further particles.)
-constexpr int64_t kWaveBlocks = int64_t(1) << 22;
-static unsigned wave_blocks(int64_t N) { return (unsigned)std::min<int64_t>((N + 3) / 4, kWaveBlocks); }
+// W lanes per particle, so that its row is read by neighbouring lanes.  (The
+// grid is bounded, and the lanes go on to further particles.)  A wave per
+// particle is the fastest from about 16 observations on, but wastes its lanes
+// on shorter rows when there are many (us at 10^6 particles with 1 / 4 / 16 /
+// 64 lanes: one observation 3.6 / 8.0 / 26 / 108, four 7.3 / 11 / 33 / 107,
+// nine 33 / 20 / 33 / 107, 25 349 / 46 / 46 / 109; at 1000 particles and 25
+// 4.3 / 3.0 / 2.8 / 2.9).
+constexpr int64_t kRowBlocks = int64_t(1) << 22;
+static unsigned row_blocks(int64_t N, int W)
+{
+    return (unsigned)std::min<int64_t>((N + 256 / W - 1) / (256 / W), kRowBlocks);
+}
 
+// sum over groups of W lanes, in every lane of the group
+template <int W>
+__device__ __forceinline__ double group_sum(double v)
+{
+#pragma unroll
+    for (int off = W / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+template <int W>
 __global__ __launch_bounds__(256) void loglik_kernel(int64_t N, int nobs, const double* __restrict__ G,
                                                      const double* __restrict__ y, double inv_sigma,
                                                      double* __restrict__ phi)
 {
-    for (int64_t q = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6); q < N; q += gridDim.x * (int64_t)4) {
+    constexpr int64_t P = 256 / W;
+    const int lane = threadIdx.x & (W - 1);
+    for (int64_t q = blockIdx.x * P + threadIdx.x / W; q < N; q += gridDim.x * P) {
         double s = 0.0;
-        for (int o = threadIdx.x & 63; o < nobs; o += 64) {
+        for (int o = lane; o < nobs; o += W) {
             const double r = (y[o] - G[q * nobs + o]) * inv_sigma;
             s += r * r;
         }
-        s = lane63_sum(s);
-        if ((threadIdx.x & 63) == 63) phi[q] = 0.5 * s;
+        if constexpr (W == 64) s = lane63_sum(s);
+        else s = group_sum<W>(s);
+        if (lane == W - 1) phi[q] = 0.5 * s;
     }
 }
 
@@ -35,7 +56,11 @@ int launch_loglik(mls2mc_ctx* ctx, int64_t N, const double* G, const double* y, 
                   hipStream_t s)
 {
     if (N == 0) return MLS2MC_OK;
-    loglik_kernel<<<wave_blocks(N), 256, 0, s>>>(N, ctx->nobs, G, y, 1.0 / ctx->prob.sigma_n, phi);
+    const int nobs = ctx->nobs;
+    const double inv_sigma = 1.0 / ctx->prob.sigma_n;
+    if (nobs <= 4) loglik_kernel<1><<<row_blocks(N, 1), 256, 0, s>>>(N, nobs, G, y, inv_sigma, phi);
+    else if (nobs <= 16) loglik_kernel<4><<<row_blocks(N, 4), 256, 0, s>>>(N, nobs, G, y, inv_sigma, phi);
+    else loglik_kernel<64><<<row_blocks(N, 64), 256, 0, s>>>(N, nobs, G, y, inv_sigma, phi);
     MLS_CHECK_HIP(hipGetLastError());
     return MLS2MC_OK;
 }
@@ -805,8 +830,15 @@ int launch_pcn_propose(int64_t N, int K, double s_pcn, int kernel, const double*
 // mode 0: tempering (Psi = beta Phi_lo); 1: bridging with zeta < 1; 2:
 // bridging at zeta = 1 (Psi = beta Phi_hi).  rwm: the random-walk kernel,
 // whose ratio also carries the N(0, I) prior term |theta|^2 / 2.
-// One wave per particle, so that rows are copied by neighbouring lanes (one
-// thread per particle copying its rows took 15 us at N = 1000, K = 50).
+// W lanes per particle, so that its rows are copied by neighbouring lanes; as
+// many as its K + nobs values occupy (us with 1 / 4 / 16 / 64 lanes at 10^5
+// particles: K = 1, one observation 3.3 / 4.5 / 10 / 34, K = 4, nine 9.7 / 6.2 /
+// 11 / 34, K = 20, nine 29 / 13 / 14 / 36, K = 50, 25 110 / 41 / 21 / 37, K = 100,
+// 49 210 / 68 / 40 / 44; at 1000 particles the last two 21 / 5.3 / 3.3 / 3.1 and
+// 41 / 7.9 / 4.0 / 3.2).  Those accept every particle; lanes that only find it
+// rejected cost as much, so many particles take fewer (10^5 particles all
+// rejected: 3.1 with one lane, 28 with 64).
+template <int W>
 __global__ __launch_bounds__(256) void pcn_accept_kernel(
     int64_t N, int K, int nobs, int mode, int rwm, double beta, double zeta, const double* __restrict__ u,
     const double* __restrict__ thn, const double* __restrict__ Gln, const double* __restrict__ Ghn,
@@ -814,9 +846,10 @@ __global__ __launch_bounds__(256) void pcn_accept_kernel(
     const int8_t* __restrict__ sth, double* __restrict__ th, double* __restrict__ Gl, double* __restrict__ Gh,
     double* __restrict__ pl, double* __restrict__ ph, uint8_t* __restrict__ acc)
 {
-    const int lane = threadIdx.x & 63;
+    constexpr int64_t P = 256 / W;
+    const int lane = threadIdx.x & (W - 1);
     const bool need_lo = mode != 2, need_hi = mode != 0;
-    for (int64_t j = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6); j < N; j += gridDim.x * (int64_t)4) {
+    for (int64_t j = blockIdx.x * P + threadIdx.x / W; j < N; j += gridDim.x * P) {
         double psi_old, psi_new;
         if (mode == 0) {
             psi_old = beta * pl[j];
@@ -830,23 +863,23 @@ __global__ __launch_bounds__(256) void pcn_accept_kernel(
         }
         if (rwm) {
             double qo = 0.0, qn = 0.0;
-            for (int k = lane; k < K; k += 64) {
+            for (int k = lane; k < K; k += W) {
                 qo += th[j * K + k] * th[j * K + k];
                 qn += thn[j * K + k] * thn[j * K + k];
             }
-            psi_old += 0.5 * wave_sum(qo);
-            psi_new += 0.5 * wave_sum(qn);
+            psi_old += 0.5 * group_sum<W>(qo);
+            psi_new += 0.5 * group_sum<W>(qn);
         }
         bool ok = true;
         if (need_lo && stl && stl[j] != 0) ok = false;
         if (need_hi && sth && sth[j] != 0) ok = false;
         const bool a = ok && (log(u[j]) < -(psi_new - psi_old));
         if (a) {
-            for (int k = lane; k < K; k += 64) th[j * K + k] = thn[j * K + k];
+            for (int k = lane; k < K; k += W) th[j * K + k] = thn[j * K + k];
             if (need_lo)
-                for (int o = lane; o < nobs; o += 64) Gl[j * nobs + o] = Gln[j * nobs + o];
+                for (int o = lane; o < nobs; o += W) Gl[j * nobs + o] = Gln[j * nobs + o];
             if (need_hi)
-                for (int o = lane; o < nobs; o += 64) Gh[j * nobs + o] = Ghn[j * nobs + o];
+                for (int o = lane; o < nobs; o += W) Gh[j * nobs + o] = Ghn[j * nobs + o];
         }
         if (lane == 0) {
             if (a && need_lo) pl[j] = pln[j];
@@ -863,9 +896,16 @@ int launch_pcn_accept(int64_t N, int K, int nobs, int mode, int rwm, double beta
                       double* Ghi, double* plo, double* phi, uint8_t* acc, hipStream_t s)
 {
     if (N == 0) return MLS2MC_OK;
-    pcn_accept_kernel<<<wave_blocks(N), 256, 0, s>>>(
-        N, K, nobs, mode, rwm, beta, zeta, u, th_new, Glo_new, Ghi_new, plo_new, phi_new, st_lo, st_hi,
-        theta, Glo, Ghi, plo, phi, acc);
+#define MLS_ACCEPT(W)                                                                                        \
+    pcn_accept_kernel<W><<<row_blocks(N, W), 256, 0, s>>>(N, K, nobs, mode, rwm, beta, zeta, u, th_new, Glo_new, \
+                                                          Ghi_new, plo_new, phi_new, st_lo, st_hi, theta, Glo, \
+                                                          Ghi, plo, phi, acc)
+    const int row = K + nobs;
+    if (row <= 4) MLS_ACCEPT(1);
+    else if (row <= 16 || (row <= 48 && N > 32768)) MLS_ACCEPT(4);
+    else if (row <= 48 || N > 32768) MLS_ACCEPT(16);
+    else MLS_ACCEPT(64);
+#undef MLS_ACCEPT
     MLS_CHECK_HIP(hipGetLastError());
     return MLS2MC_OK;
 }
