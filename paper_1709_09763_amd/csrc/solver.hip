@@ -1401,20 +1401,34 @@ static int default_block(int l)
     return 1024;
 }
 
-// LDS budget of level l in bytes.  The library's own choice beside the
-// default block: FP64 at h = 1/128 takes all there is (the fine level's FP32
-// weights of the V-cycle then fit: 5.43 ms per 512 solves against 5.78 at
-// 64 KiB), the mixed form none there (3.72 ms against 4.07; the coarse levels'
-// flat accesses cost more than L2 hits), else 64 KiB.  The row walks of 1024
-// threads take no residency (lds_bytes_for).
-static int64_t lds_budget(const mls2mc_ctx* ctx, int l, bool mixed)
+// The library's own launch shape for N particles of level l (or of a list with
+// finest level l): block, workgroups per CU, LDS budget in bytes.  FP64 at
+// h = 1/128 takes all the LDS there is (the fine level's FP32 weights of the
+// V-cycle then fit: 5.43 ms per 512 solves against 5.78 at 64 KiB), the mixed
+// form none there (3.72 ms against 4.07; the coarse levels' flat accesses cost
+// more than L2 hits), else 64 KiB.  The row walks of 1024 threads take no
+// residency (lds_bytes_for).  The mixed form at h = 1/128 keeps four workgroups
+// of 512 threads per CU where one per CU would leave a second round mostly
+// empty (ms, 512 threads -> 1024: 256 particles 2.38 -> 1.81, 257 2.62 -> 2.84,
+// 320 2.88 -> 3.22, 384 3.16 -> 3.28, 448 3.51 -> 3.34, 513 4.89 -> 4.49; in FP64
+// the wider workgroup is the faster one there too, 4.02 -> 4.00 at 257).
+struct OwnShape {
+    int block, per_cu;
+    int64_t lds;
+};
+static OwnShape own_shape(const mls2mc_ctx* ctx, int l, int64_t N, bool mixed)
+{
+    if (l <= 6) return {default_block(l), 8, 65536};
+    if (mixed && l == 7 && N > ctx->n_cu && 2 * N <= 3 * (int64_t)ctx->n_cu) return {512, 4, 65536};
+    return {1024, 1, mixed ? 0 : l == 7 ? ctx->max_lds : 65536};
+}
+
+// LDS budget of level l in bytes; own: the library's choice beside its own block
+static int64_t lds_budget(const mls2mc_ctx* ctx, int l, int64_t own)
 {
     int64_t budget = ctx->solver_lds[l];
     if (budget < 0) return 0;
-    if (budget == 0) {
-        const bool own = ctx->solver_block[l] == 0 && l >= 7;
-        budget = own && mixed ? 0 : own && l == 7 ? ctx->max_lds : 65536;
-    }
+    if (budget == 0) budget = ctx->solver_block[l] == 0 ? own : 65536;
     return budget < ctx->max_lds ? budget : ctx->max_lds;
 }
 
@@ -1460,11 +1474,10 @@ static Common make_common(const mls2mc_ctx* ctx, int l)
 // launch takes no more LDS than the budget (or than the inverse's 648 bytes
 // under a smaller one), so the workgroups per CU that a budget was chosen
 // for still fit.
-static size_t lds_bytes_for(const mls2mc_ctx* ctx, int l, bool mixed, int bs, bool walks, int64_t* alloc_elems,
-                            int* cinv_lds, int64_t* ring_off)
+static size_t lds_bytes_for(const mls2mc_ctx* ctx, int l, bool mixed, int bs, int64_t budget, bool walks,
+                            int64_t* alloc_elems, int* cinv_lds, int64_t* ring_off)
 {
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
-    int64_t budget = lds_budget(ctx, l, mixed);
     // the row walks' rows come first: the residency gets what is left
     const int64_t ring = walks ? walk_ring_elems(bs, l) : 0;
     const int64_t ring_bytes = ring * (int64_t)esz;
@@ -1504,9 +1517,10 @@ int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
     int64_t slot = solver_slot_elems(l, mixed);
     slot = (slot + 63) & ~int64_t(63);  // 256/512-byte aligned slots
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
-    int bs = ctx->solver_block[l] ? ctx->solver_block[l] : default_block(l);
-    int64_t grid = ctx->solver_grid[l] ? ctx->solver_grid[l]
-                                       : (int64_t)dev_cus * (l <= 6 ? 8 : ctx->solver_block[l] ? 4 : 1);
+    OwnShape shape = own_shape(ctx, l, a.N, mixed);
+    if (ctx->solver_block[l]) shape = {ctx->solver_block[l], l <= 6 ? 8 : 4, 65536};
+    const int bs = shape.block;
+    int64_t grid = ctx->solver_grid[l] ? ctx->solver_grid[l] : (int64_t)dev_cus * shape.per_cu;
     // cap the slot workspace at 16 GiB
     const int64_t cap = (int64_t)((16ull << 30) / (slot * esz));
     if (grid > cap) grid = cap;
@@ -1520,7 +1534,8 @@ int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
     P.queue = ctx->d_queue;
     P.C = make_common(ctx, l);
     const bool fused = launch_walks(l, bs, P.C.nu);
-    const size_t lds = lds_bytes_for(ctx, l, mixed, bs, fused, &P.lds_elems, &P.cinv_lds, &P.ring_off);
+    const size_t lds = lds_bytes_for(ctx, l, mixed, bs, lds_budget(ctx, l, shape.lds), fused, &P.lds_elems,
+                                     &P.cinv_lds, &P.ring_off);
     ProfRec rec;
     if (ctx->prof_on) {
         if (!P.iters) {  // the iteration totals need per-particle counts
@@ -1560,10 +1575,6 @@ int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
 // level first); lmax: finest level in the list; total: sum of N.
 static void list_shape(const mls2mc_ctx* ctx, int lmax, int64_t total, bool mixed, int64_t* grid,
                        int64_t* slot, int* bs);
-static int list_block(const mls2mc_ctx* ctx, int lmax)
-{
-    return ctx->list_block ? ctx->list_block : default_block(lmax);
-}
 
 int launch_solve_list(mls2mc_ctx* ctx, const SolveItem* items_dev, int n_items, int64_t total, int lmax,
                       bool walked, bool mixed, hipStream_t s)
@@ -1587,7 +1598,8 @@ int launch_solve_list(mls2mc_ctx* ctx, const SolveItem* items_dev, int n_items, 
     P.queue = ctx->d_queue;
     P.C = make_common(ctx, lmax);
     const bool fused = walked;
-    const size_t lds = lds_bytes_for(ctx, lmax, mixed, bs, fused, &P.lds_elems, &P.cinv_lds, &P.ring_off);
+    const int64_t budget = lds_budget(ctx, lmax, own_shape(ctx, lmax, total, mixed).lds);
+    const size_t lds = lds_bytes_for(ctx, lmax, mixed, bs, budget, fused, &P.lds_elems, &P.cinv_lds, &P.ring_off);
     dim3 g((unsigned)grid);
     // items of h = 1/64 and finer walk columns in the CG stencil pass (the
     // instance decides per item)
@@ -1664,14 +1676,16 @@ static void list_shape(const mls2mc_ctx* ctx, int lmax, int64_t total, bool mixe
     int64_t sl = solver_slot_elems(lmax, mixed);
     sl = (sl + 63) & ~int64_t(63);
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
-    int64_t g = ctx->list_grid ? ctx->list_grid : (int64_t)ctx->n_cu * (lmax >= 7 && !ctx->list_block ? 1 : 4);
+    const OwnShape shape = own_shape(ctx, lmax, total, mixed);
+    int64_t g = ctx->list_grid ? ctx->list_grid
+                               : (int64_t)ctx->n_cu * (ctx->list_block ? 4 : std::min(4, shape.per_cu));
     const int64_t cap = (int64_t)((16ull << 30) / (sl * esz));
     if (g > cap) g = cap;
     if (g > total) g = total;
     if (g < 1) g = 1;
     *grid = g;
     *slot = sl;
-    *bs = list_block(ctx, lmax);
+    *bs = ctx->list_block ? ctx->list_block : shape.block;
 }
 
 int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vector<ListChunk>& out,
@@ -1746,7 +1760,8 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
         bool split = true;
         for (const Piece& pc : ch)
             if (pc.it.l >= 8)
-                split = split && launch_walks(pc.it.l, list_block(ctx, pc.it.l), make_common(ctx, pc.it.l).nu);
+                split = split && launch_walks(pc.it.l, ctx->list_block ? ctx->list_block : default_block(pc.it.l),
+                                              make_common(ctx, pc.it.l).nu);
         size_t kap_off = 0;
         for (size_t i = 0; i < ch.size(); ++i) {
             const FwdItem& it = ch[i].it;
