@@ -221,7 +221,7 @@ struct ListChunk {  // one prepared grouped GEMM and the solves of its items
     const SolveItem* solve;
     int n;
     int64_t tiles;
-    ListGroup group[2];  // work-list launches: the walked levels on their own, the others
+    ListGroup group[3];  // work-list launches: the walked levels, the others, h = 1/4 and 1/2
     std::vector<ListLevel> levels;
 };
 int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items, std::vector<ListChunk>& out, hipStream_t s);

@@ -1312,7 +1312,11 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_kernel(SolveParams P
 // solve_kernel.  Slots are sized for the finest level in the list.  WK = 2:
 // every item is of h = 1/256 or finer and runs the fused row walks (the
 // separate passes beside them in one kernel, inlined or called, cost it
-// hundreds of spilled registers).
+// hundreds of spilled registers).  FP64 lists of the small levels alone (WK = 0)
+// take fixed shares instead: a solve at h = 1/2 or 1/4, exact, is not much longer
+// than the draw of its number (us, 20000 particles on each of them: drawn 675, in
+// runs of four 557, of sixteen 623, shares 528).  The mixed form's iterations
+// differ too much for that (drawn 1361, runs of four 1485, shares 1964).
 struct ListParams {
     const SolveItem* items;
     int n_items;
@@ -1340,7 +1344,7 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_list_kernel(ListPara
         __syncthreads();
         return v;
     };
-    for (int64_t p = draw(); p < P.total; p = draw()) {
+    auto solve = [&](int64_t p) {
         int lo = 0, hi = P.n_items - 1;  // last item with base <= p
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -1374,7 +1378,12 @@ __global__ __launch_bounds__(BS) MLS_SOLVER_ATTR void solve_list_kernel(ListPara
             if constexpr (kVisit7<BS, WK>) solve_one_f64_here<BS, WK, false>(M, J, P.C, red);
             else solve_one_f64<BS, WK, false>(M, J, P.C, red);
         }
+    };
+    if constexpr (WK == 0 && !MIXED) {
+        for (int64_t p = blockIdx.x; p < P.total; p += gridDim.x) solve(p);
+        return;
     }
+    for (int64_t p = draw(); p < P.total; p = draw()) solve(p);
     // as in solve_kernel: the last workgroup to finish resets the counter
     if (threadIdx.x == 0) {
         __threadfence();
@@ -1756,7 +1765,9 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
         lc.n = (int)ch.size();
         lc.tiles = 0;
         // Particles of h = 1/256 and finer get a launch of their own, with the
-        // fused row walks, so a batch solves them as single forwards do.
+        // fused row walks, so a batch solves them as single forwards do; those
+        // of h = 1/4 and 1/2 one with their small workgroups (20000 of each
+        // beside four of h = 1/128, mixed: 6.2 ms in one launch, 2.7 in two).
         bool split = true;
         for (const Piece& pc : ch)
             if (pc.it.l >= 8)
@@ -1796,7 +1807,7 @@ int prepare_list(mls2mc_ctx* ctx, const std::vector<FwdItem>& items_in, std::vec
                 lv.total += it.N;
                 ++lv.n;
             } else {
-                ListGroup& gr = lc.group[split && it.l >= 8 ? 0 : 1];
+                ListGroup& gr = lc.group[split && it.l >= 8 ? 0 : it.l >= 3 ? 1 : 2];
                 v.base = gr.total;
                 gr.total += it.N;
                 if (gr.n++ == 0) gr.first = (int)i;
@@ -1829,7 +1840,7 @@ int enqueue_list(mls2mc_ctx* ctx, const std::vector<ListChunk>& chunks, hipStrea
     const bool mixed = ctx->prob.precision == MLS2MC_MIXED;
     for (const auto& lc : chunks) {
         MLS_TRY(launch_kl_list(ctx, lc.gemm, lc.n, lc.tiles, s));
-        for (int g = 0; g < 2; ++g)
+        for (int g = 0; g < 3; ++g)
             MLS_TRY(launch_solve_list(ctx, lc.solve + lc.group[g].first, lc.group[g].n, lc.group[g].total,
                                       lc.group[g].lmax, g == 0, mixed, s));
         for (const ListLevel& lv : lc.levels)

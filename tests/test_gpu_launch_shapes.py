@@ -39,3 +39,30 @@ def test_mixed_h128_around_one_particle_per_cu(per_cu):
     G2, p2, _, _ = c.forward_field(l, dev, True)
     assert rel_err(host(G), host(G2)) < 1e-6 and rel_err(host(p), host(p2)) < 1e-6
     c.close()
+
+
+@pytest.mark.parametrize("precision", [P.FP64, P.MIXED])
+@pytest.mark.parametrize("n1,n2,n7", [(1, 0, 0), (3, 4, 1), (16384, 1, 2), (9001, 8003, 0), (140001, 17, 3)])
+def test_batch_of_the_smallest_levels(precision, n1, n2, n7):
+    """h = 1/2 and 1/4 in a launch of their own, beside h = 1/128: each item equals
+    its single forward (the same solve of each particle, with its status: in the
+    mixed form not every particle of these two levels reaches the tolerance)."""
+    device()
+    case(f"batch precision={precision} h=1/2: {n1}, 1/4: {n2}, 1/128: {n7}")
+    c = P.Context(1, 7, 8, 1.0, 0.3, 4, 0.01, precision=precision)
+    items = []
+    for q, (l, N) in enumerate([(1, n1 // 2), (2, n2), (7, n7), (1, n1 - n1 // 2)]):
+        th = to_dev(inputs.theta_batch(40 + q, max(N, 1), 8)[:N])
+        items.append(dict(l=l, theta=th, G_out=torch.full((N, 16), np.nan, dtype=torch.float64, device="cuda:0"),
+                          status_out=torch.full((N,), -1, dtype=torch.int8, device="cuda:0")))
+    for _ in range(2):  # the hand-out counter resets itself
+        P.mls2mc_forward_batch(c.h, items)
+    for it in items:
+        if it["theta"].shape[0] == 0:
+            continue
+        G, st, _ = c.forward(it["l"], it["theta"], True)
+        st, good = host(st), host(st) == 0
+        np.testing.assert_array_equal(host(it["status_out"]), st)
+        assert good.mean() > 0.9
+        assert rel_err(host(it["G_out"])[good], host(G)[good]) < 1e-11
+    c.close()
