@@ -534,7 +534,8 @@ int mls2mc_autotune(mls2mc_ctx* ctx, int l, int64_t N, double* best_ms, void* st
  * launch shapes of its own, and so does h = 1/128 of the FP64 Dirichlet
  * problem with at most 128 observations, in launches that do not return the
  * field; the autotuner tries it first and returns it as {0, default block,
- * 0, 0}.                                                                   */
+ * 0, 0}.  Launches at h = 1/128 that do return the field take the library's
+ * own shape of the general solver then.                                    */
 int mls2mc_get_launch(const mls2mc_ctx* ctx, int l, int* grid, int* block, int* nu, int* lds_bytes);
 int mls2mc_set_launch(mls2mc_ctx* ctx, int l, int grid, int block, int nu, int lds_bytes);
 

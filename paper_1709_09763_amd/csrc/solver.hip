@@ -1432,12 +1432,12 @@ static OwnShape own_shape(const mls2mc_ctx* ctx, int l, int64_t N, bool mixed)
     return {1024, 1, mixed ? 0 : l == 7 ? ctx->max_lds : 65536};
 }
 
-// LDS budget of level l in bytes; own: the library's choice beside its own block
-static int64_t lds_budget(const mls2mc_ctx* ctx, int l, int64_t own)
+// LDS budget of level l in bytes; fallback: that of the launch's shape
+static int64_t lds_budget(const mls2mc_ctx* ctx, int l, int64_t fallback)
 {
     int64_t budget = ctx->solver_lds[l];
     if (budget < 0) return 0;
-    if (budget == 0) budget = ctx->solver_block[l] == 0 ? own : 65536;
+    if (budget == 0) budget = fallback;
     return budget < ctx->max_lds ? budget : ctx->max_lds;
 }
 
@@ -1527,7 +1527,10 @@ int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)
     slot = (slot + 63) & ~int64_t(63);  // 256/512-byte aligned slots
     const size_t esz = mixed ? sizeof(float) : sizeof(double);
     OwnShape shape = own_shape(ctx, l, a.N, mixed);
-    if (ctx->solver_block[l]) shape = {ctx->solver_block[l], l <= 6 ? 8 : 4, 65536};
+    // (the default block named and nothing else set is the library's own choice:
+    // what the autotuner returns for the resident solver, which has left this
+    // launch to the general one because it asks for the field)
+    if (ctx->solver_block[l] && !resident_level(ctx, l)) shape = {ctx->solver_block[l], l <= 6 ? 8 : 4, 65536};
     const int bs = shape.block;
     int64_t grid = ctx->solver_grid[l] ? ctx->solver_grid[l] : (int64_t)dev_cus * shape.per_cu;
     // cap the slot workspace at 16 GiB

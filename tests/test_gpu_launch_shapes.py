@@ -66,3 +66,28 @@ def test_batch_of_the_smallest_levels(precision, n1, n2, n7):
         assert good.mean() > 0.9
         assert rel_err(host(it["G_out"])[good], host(G)[good]) < 1e-11
     c.close()
+
+
+def test_autotuners_name_for_the_resident_solver_with_the_field():
+    """{0, 1024, 0, 0} at h = 1/128 is the library's own choice: a launch that
+    returns the field takes the same shape as with nothing set, so the same
+    device memory and bitwise the same results."""
+    device()
+    l, N = 7, 1024
+    case(f"h=1/128 FP64 field N={N}, default block named")
+    G, p = torch.empty((N, 16), dtype=torch.float64, device="cuda:0"), None
+    kap = to_dev(_kappa(5, 4, l)).repeat(N // 4, 1)
+    out, used = [], []
+    for shape in ((0, 0, 0, 0), (0, 0, 0, 0), (0, 1024, 0, 0)):  # the first for the runtime's own allocations
+        c = P.Context(l, l, 4, 1.0, 0.3, 4, 0.01)
+        c.set_launch(l, *shape)
+        p = torch.empty((N, P.mls2mc_ctx_n_unknowns(c.h, l)), dtype=torch.float64, device="cuda:0")
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        P.mls2mc_forward_field(c.h, l, kap, G, p)
+        torch.cuda.synchronize()
+        used.append(before - torch.cuda.mem_get_info()[0])
+        out.append((G.clone(), p[:8].clone()))
+        c.close()
+    assert used[2] == used[1], used
+    assert torch.equal(out[1][0], out[2][0]) and torch.equal(out[1][1], out[2][1])
