@@ -528,14 +528,16 @@ int mls2mc_autotune(mls2mc_ctx* ctx, int l, int64_t N, double* best_ms, void* st
  * lds_bytes 0 = built-in default; lds_bytes -1 = no LDS residency, else
  * the per-workgroup LDS budget in bytes, at most the device's LDS per
  * workgroup less 1 KiB; 160 KiB on gfx950), e.g. to restore tuned
- * schedules cached by the caller.  With everything default (nu 1 counts as
- * default), or everything but the block and that one the level's default
- * block, levels h = 1/8 .. 1/64 run the register-resident solver, which has
- * launch shapes of its own, and so does h = 1/128 of the FP64 Dirichlet
- * problem with at most 128 observations, in launches that do not return the
- * field; the autotuner tries it first and returns it as {0, default block,
- * 0, 0}.  Launches at h = 1/128 that do return the field take the library's
- * own shape of the general solver then.                                    */
+ * schedules cached by the caller.  Dirichlet launches of 1024 threads at
+ * h = 1/256 and finer with nu 1 hold fixed parts of the solve in the LDS
+ * (up to 150 KiB) whatever lds_bytes says.  With everything default (nu 1
+ * counts as default), or everything but the block and that one the level's
+ * default block, levels h = 1/8 .. 1/64 run the register-resident solver,
+ * which has launch shapes of its own, and so does h = 1/128 of the FP64
+ * Dirichlet problem with at most 128 observations, in launches that do not
+ * return the field; the autotuner tries it first and returns it as
+ * {0, default block, 0, 0}.  Launches at h = 1/128 that do return the field
+ * take the library's own shape of the general solver then.                 */
 int mls2mc_get_launch(const mls2mc_ctx* ctx, int l, int* grid, int* block, int* nu, int* lds_bytes);
 int mls2mc_set_launch(mls2mc_ctx* ctx, int l, int grid, int block, int nu, int lds_bytes);
 

@@ -1490,7 +1490,7 @@ static size_t lds_bytes_for(const mls2mc_ctx* ctx, int l, bool mixed, int bs, in
     // the row walks' rows come first: the residency gets what is left
     const int64_t ring = walks ? walk_ring_elems(bs, l) : 0;
     const int64_t ring_bytes = ring * (int64_t)esz;
-    if (walks && bs == 1024) {  // kVisit7: the levels below h = 1/64 instead of any residency
+    if (walks && bs == 1024) {  // kVisit7: the levels below h = 1/64 instead of any residency (solver_lds_fixed)
         *alloc_elems = 0;
         *cinv_lds = 0;
         *ring_off = (int64_t)((mixed ? sizeof(Levels5<float>) : sizeof(Levels5<double>)) / esz);
@@ -1512,6 +1512,11 @@ static size_t lds_bytes_for(const mls2mc_ctx* ctx, int l, bool mixed, int bs, in
 static bool launch_walks(int l, int bs, int nu)
 {
     return nu == 1 && l >= 8 && bs % (1 << (l - 1)) == 0;
+}
+
+bool solver_lds_fixed(const mls2mc_ctx* ctx, int l, int bs, int nu)
+{
+    return ctx->prob.bc != MLS2MC_BC_FLOW_CELL && launch_walks(l, bs, nu) && bs == 1024;
 }
 
 int launch_solve(mls2mc_ctx* ctx, const SolveArgs& a, hipStream_t s)

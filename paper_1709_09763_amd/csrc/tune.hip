@@ -46,7 +46,7 @@ extern "C" int mls2mc_set_launch(mls2mc_ctx* ctx, int l, int grid, int block, in
                 "set_launch: block must be 0 (auto), 64, 128, 256, 512 or 1024");
     MLS_REQUIRE(nu >= 0 && nu <= 4, "set_launch: nu must be 0 (default 1) .. 4");
     MLS_REQUIRE(lds_bytes == -1 || (lds_bytes >= 0 && lds_bytes <= ctx->max_lds),
-                "set_launch: lds_bytes must be -1 (none), 0 (default 64 KiB) or up to the device's "
+                "set_launch: lds_bytes must be -1 (none), 0 (the library's choice) or up to the device's "
                 "LDS per workgroup less 1 KiB");
     ctx->solver_grid[l] = grid;
     ctx->solver_block[l] = block;
@@ -100,7 +100,8 @@ extern "C" int mls2mc_autotune(mls2mc_ctx* ctx, int l, int64_t N, double* best_m
     else { wpc = {1, 2, 4}; blocks = {256, 512, 1024}; }
     // LDS budgets: none, the default 64 KiB, 80 KiB (still two workgroups per
     // CU on a 160 KiB LDS) and the device maximum; a budget that gives the
-    // same residency as a smaller one is skipped
+    // same residency as a smaller one is skipped, and launches whose LDS does
+    // not depend on it are timed at the default alone
     std::vector<int> ldsc = {-1, 0};
     {
         const int64_t esz_ = (int64_t)esz;
@@ -127,6 +128,7 @@ extern "C" int mls2mc_autotune(mls2mc_ctx* ctx, int l, int64_t N, double* best_m
             ctx->solver_nu[l] = nu;
             for (int b : blocks) {
                 if (rc != MLS2MC_OK) break;
+                if (lds != 0 && solver_lds_fixed(ctx, l, b, nu)) continue;
                 int64_t last_grid = -1;
                 for (int w : wpc) {
                     int64_t g = std::min<int64_t>((int64_t)w * cu, N);

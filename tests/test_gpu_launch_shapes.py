@@ -91,3 +91,21 @@ def test_autotuners_name_for_the_resident_solver_with_the_field():
         c.close()
     assert used[2] == used[1], used
     assert torch.equal(out[1][0], out[2][0]) and torch.equal(out[1][1], out[2][1])
+
+
+@pytest.mark.parametrize("precision", [P.FP64, P.MIXED])
+def test_lds_budget_of_the_walking_workgroups(precision):
+    """1024 threads at V(1,1) from h = 1/256 on: the budget changes nothing, and
+    the autotuner does not return one for them."""
+    device()
+    case(f"h=1/256 precision={precision}: budgets of 1024 threads")
+    c = P.Context(8, 8, 4, 1.0, 0.3, 4, 0.01, precision=precision)
+    th = to_dev(inputs.theta_batch(60, 5, 4))
+    G = []
+    for lds in (0, -1, 65536, 81920):
+        c.set_launch(8, 4, 1024, 1, lds)
+        G.append(c.forward(8, th))
+    assert all(torch.equal(G[0], g) for g in G[1:])
+    _, (grid, block, nu, lds) = c.autotune(8, 24)
+    assert block != 1024 or nu != 1 or lds == 0
+    c.close()
