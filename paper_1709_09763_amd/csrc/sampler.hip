@@ -74,14 +74,23 @@ int launch_loglik(mls2mc_ctx* ctx, int64_t N, const double* G, const double* y, 
 //  * up to kStepSmall particles one workgroup keeps d in registers and an
 //    evaluation is one exponential per element and one barrier (both sums
 //    reduced by DPP together; 130 us -> 27 us at N = 200, where four barriers
-//    and shuffles took 2 us per evaluation);
+//    and shuffles took 2 us per evaluation).  From 2049 particles on, where an
+//    evaluation takes one CU 2.6 us and more, it first brackets the root in
+//    about a dozen evaluations, and the bisection then evaluates only the
+//    midpoints inside the bracket (ESS does not grow with t);
 //  * beyond, a launch evaluates all midpoints of the next L bisection levels
 //    (2^L - 1, every one by its own workgroups) and the next launch walks
 //    down them: 64 / L launches instead of 64 passes of one workgroup
 //    (474 us -> 76 us at N = 16384: 11 launches of 6.2 us).
-// Both take the midpoints and the comparisons of plain bisection.
+// Both take the midpoints and the comparisons of plain bisection.  Where the
+// line lies (us a call with its launches, inside / at an end; one workgroup
+// with plain bisection in global memory, launches, one workgroup with the
+// bracket): 2049 particles 150 / 13, 54 / 41-46, 52 / 13; 8192 283 / 18-22,
+// 67 / 43-46, 80 / 13; 16384 460 / 28-34, 76 / 45-50, about 150 / 19.  Beyond
+// 8192 an end costs up to 25 us more than in one workgroup (until about 30000),
+// a step inside 200 us and more less.
 constexpr int kNS = 1024;
-constexpr int64_t kStepSmall = 2048;
+constexpr int64_t kStepSmall = 8192;
 
 struct StepIn {
     int64_t N;
@@ -149,13 +158,14 @@ __global__ __launch_bounds__(BS) void next_step_small_kernel(StepIn A)
     const double tmin = A.eps < tmax ? A.eps : tmax;
     double t, e;
     bool at_end = false;
-    if ((e = ess(tmax)) >= A.tau) {
+    const double e_end = ess(tmax);
+    if ((e = e_end) >= A.tau) {
         t = tmax;
         at_end = true;
     } else if ((e = ess(tmin)) <= A.tau) {
         t = tmin;
         at_end = (tmin == tmax);
-    } else {
+    } else if constexpr (PER <= 2) {
         double lo = tmin, hi = tmax, elo = e;
         double2 slo = s;
         for (int it = 0; it < 64; ++it) {
@@ -169,6 +179,62 @@ __global__ __launch_bounds__(BS) void next_step_small_kernel(StepIn A)
             } else {
                 hi = mid;
             }
+        }
+        t = lo;
+        e = elo;
+        s = slo;
+    } else {
+        double known = tmin, out = tmax, elo = e;  // ESS(known) = elo >= tau > ESS(out)
+        double2 slo = s;
+        auto in = [&](double tt, double et) -> bool {
+            if (!(et >= A.tau)) {
+                out = tt;
+                return false;
+            }
+            known = tt;
+            elo = et;
+            slo = s;
+            return true;
+        };
+        // the root of log(ESS / tau) over log t by Chandrupatla's method (inverse
+        // quadratic interpolation where it is safe, else the bracket's middle)
+        double x1 = log(tmax), f1 = log(e_end / A.tau), x2 = log(tmin), f2 = log(e / A.tau), x3 = x1, f3 = f1;
+        double at = 0.5;
+        for (int it = 0; it < 48 && isfinite(f1) && isfinite(f2); ++it) {
+            const double x = x1 + at * (x2 - x1), tt = exp(x);
+            if (!(tt > known && tt < out)) break;
+            const double et = ess(tt), f = log(et / A.tau);
+            in(tt, et);
+            if ((f >= 0.0) == (f1 >= 0.0)) {
+                x3 = x1;
+                f3 = f1;
+            } else {
+                x3 = x2;
+                f3 = f2;
+                x2 = x1;
+                f2 = f1;
+            }
+            x1 = x;
+            f1 = f;
+            const double edge = 0x1p-50 / fabs(x2 - x1);  // a bracket of a few adjacent numbers ends it
+            if (!(edge < 0.5)) break;
+            const double xi = (x1 - x2) / (x3 - x2), phi = (f1 - f2) / (f3 - f2);
+            at = 0.5;
+            if (phi * phi < xi && (1.0 - phi) * (1.0 - phi) < 1.0 - xi)
+                at = f1 / (f2 - f1) * (f3 / (f2 - f3)) + (x3 - x1) / (x2 - x1) * (f1 / (f3 - f1)) * (f2 / (f3 - f2));
+            at = fmin(fmax(at, edge), 1.0 - edge);
+        }
+        // the bisection, whose midpoints outside the bracket are decided
+        double lo = tmin, hi = tmax;
+        for (int it = 0; it < 64; ++it) {
+            const double mid = 0.5 * (lo + hi);
+            if (mid == lo || mid == hi) break;
+            if (mid <= known || (mid < out && in(mid, ess(mid)))) lo = mid;
+            else hi = mid;
+        }
+        if (known != lo) {
+            elo = ess(lo);
+            slo = s;
         }
         t = lo;
         e = elo;
@@ -375,7 +441,9 @@ int launch_next_step(mls2mc_ctx* ctx, int64_t N, const double* d, double scale, 
         if (N <= 256) next_step_small_kernel<256, 1><<<1, 256, 0, s>>>(A);
         else if (N <= 512) next_step_small_kernel<512, 1><<<1, 512, 0, s>>>(A);
         else if (N <= 1024) next_step_small_kernel<512, 2><<<1, 512, 0, s>>>(A);
-        else next_step_small_kernel<1024, 2><<<1, 1024, 0, s>>>(A);
+        else if (N <= 2048) next_step_small_kernel<1024, 2><<<1, 1024, 0, s>>>(A);
+        else if (N <= 4096) next_step_small_kernel<1024, 4><<<1, 1024, 0, s>>>(A);
+        else next_step_small_kernel<1024, 8><<<1, 1024, 0, s>>>(A);
         MLS_CHECK_HIP(hipGetLastError());
         return MLS2MC_OK;
     }
