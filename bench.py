@@ -56,12 +56,28 @@ TUNED_H64 = os.path.join(TUNED_DIR, "mi355x_h8-64_K50_J1000.json")
 TUNED_H512 = os.path.join(TUNED_DIR, "mi355x_h16-512_K200_J8192.json")
 
 
+def solver_sources():
+    """solver.hip and the files of its folder that it includes, directly or not"""
+    import re
+    csrc = os.path.join(ROOT, "paper_1709_09763_amd", "csrc")
+    found, todo = [], ["solver.hip"]
+    while todo:
+        f = todo.pop()
+        if f in found:
+            continue
+        found.append(f)
+        src = open(os.path.join(csrc, f)).read()
+        todo += [g for g in re.findall(r'^\s*#\s*include\s+"([^"]+)"', src, re.M) if os.path.exists(os.path.join(csrc, g))
+                 and "/" not in g]
+    return [os.path.join(csrc, f) for f in sorted(found)]
+
+
 def solver_sha():
     """first 16 hex digits of sha256 over the solver's sources"""
     import hashlib
     h = hashlib.sha256()
-    for f in ("solver.hip", "common.h"):
-        h.update(open(os.path.join(ROOT, "paper_1709_09763_amd", "csrc", f), "rb").read())
+    for f in solver_sources():
+        h.update(open(f, "rb").read())
     return h.hexdigest()[:16]
 
 
