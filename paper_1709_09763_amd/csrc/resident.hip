@@ -30,9 +30,9 @@
 // The coarse level h = 1/32 of an h = 1/64 solve is spread over the whole
 // workgroup (one row pair per thread); the levels from h = 1/16 down run in
 // the first wave alone, without barriers, and h = 1/4 is solved with its
-// inverse.  The workgroup is the particle: the grid has one per particle, no
-// global workspace, and the hardware's dispatch evens out the iteration
-// counts.
+// inverse (the flow cell: visited by one matrix).  The workgroup is the
+// particle: the grid has one per particle, no global workspace, and the
+// hardware's dispatch evens out the iteration counts.
 //
 // Identities used (all exact in exact arithmetic): after the first red sweep
 // from z = 0 the red equations hold, so after the black sweep the red
@@ -223,7 +223,8 @@ resident_kernel(ResParams A)
             k2 = m.rs;
         }
         wave_order();
-        exact_build<FLOW>(k2, m.cinv);
+        if constexpr (FLOW) visit2_build(k2, m.cinv);
+        else exact_build(k2, m.cinv);
     }
 #undef MLS_LDS_CELL
     order<NT>();

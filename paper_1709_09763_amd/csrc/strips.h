@@ -234,11 +234,11 @@ struct Exact {
 
 // inverse of the h = 1/4 operator by Gauss-Jordan sweeps in place (an
 // M-matrix: no pivoting); one wave, lane u < N holds row u in registers and
-// stores it as column u of A (the inverse is symmetric)
-template <bool FLOW, typename T>
+// stores it as column u of A (the inverse is symmetric).  Dirichlet problem.
+template <typename T>
 __device__ __forceinline__ void exact_build(const T* kap, double* A, int t = threadIdx.x)
 {
-    using E = Exact<FLOW>;
+    using E = Exact<false>;
     constexpr int N = E::N;
     const int u = t < N ? t : N - 1;
     const int i = u % 3 + 1, j = u / 3 + E::j0;
@@ -277,7 +277,72 @@ __device__ __forceinline__ void exact_build(const T* kap, double* A, int t = thr
         for (int v = 0; v < N; ++v) A[N * v + u] = a[v];
 }
 
-// e2 = A^{-1} (restriction of the level h = 1/8's red residuals); one wave
+// The flow cell's h = 1/4 visit as a matrix: V(1,1) there and the exact
+// tridiagonal solve of h = 1/2, as the general solver ends its cycle, so that
+// both need the same iterations and stop equally close to the solution (with
+// the exact inverse in its place the cycle was a little stronger, and stopped
+// with up to 1.5 times the error).  One wave; lane u < 15 holds row u, every
+// column's value at unknown u, through the sweeps (neighbours by moves within
+// the row of 16 lanes), and stores it as column u of A (the visit is
+// symmetric).  kap: the coefficients of h = 1/4.
+template <typename T>
+__device__ __forceinline__ void visit2_build(const T* kap, double* A, int t = threadIdx.x)
+{
+    const int u = t < 15 ? t : 14;
+    const int i = u % 3 + 1, j = u / 3;
+    auto lo = [&](int ii, int jj) { return (jj >= 0 && jj < 4) ? (double)kap[2 * (4 * jj + ii)] : 0.0; };
+    auto up = [&](int ii, int jj) { return (jj >= 0 && jj < 4) ? (double)kap[2 * (4 * jj + ii) + 1] : 0.0; };
+    double we = 0.5 * (lo(i, j) + up(i, j - 1)), ww = 0.5 * (lo(i - 1, j) + up(i - 1, j - 1));
+    const double wn = 0.5 * (up(i, j) + lo(i - 1, j)), ws = 0.5 * (up(i, j - 1) + lo(i - 1, j - 1));
+    const double inv = 1.0 / (ww + we + ws + wn);
+    if (i == 1) ww = 0.0;  // into the boundary columns
+    if (i == 3) we = 0.0;
+    const bool red = !((i + j) & 1);
+    auto nb = [&](double x) {
+        return (ww * dpp<0x111>(x) + we * dpp<0x101>(x)) + (ws * dpp<0x113>(x) + wn * dpp<0x103>(x));
+    };
+    // h = 1/2: unknowns (1, 0), (1, 1), (1, 2), in every lane
+    auto clo = [&](int ii, int jj) {
+        return 0.25 * (lo(2 * ii, 2 * jj) + lo(2 * ii + 1, 2 * jj) + lo(2 * ii + 1, 2 * jj + 1) + up(2 * ii + 1, 2 * jj));
+    };
+    auto cup = [&](int ii, int jj) {
+        return 0.25 * (up(2 * ii, 2 * jj) + up(2 * ii, 2 * jj + 1) + up(2 * ii + 1, 2 * jj + 1) + lo(2 * ii, 2 * jj + 1));
+    };
+    const double e0 = 0.5 * (clo(0, 0) + cup(1, 0)), e1 = 0.5 * (clo(0, 1) + cup(1, 1));
+    const double d0 = 0.5 * (clo(0, 0) + clo(1, 0)) + e0;
+    const double d1 = 0.5 * (clo(0, 1) + cup(0, 0) + clo(1, 1) + cup(1, 0)) + e0 + e1;
+    const double d2 = 0.5 * (cup(0, 1) + cup(1, 1)) + e1;
+    const double r0 = 1.0 / d0, r1 = 1.0 / (d1 - e0 * e0 * r0), r2 = 1.0 / (d2 - e1 * e1 * r1);
+    // a red node's correction: that of its own h = 1/2 node (column 2), or half
+    // of the one at the other end of its diagonal edge (the boundary's is zero)
+    const int J = i == 3 ? (j - 1) / 2 : i == 1 ? (j + 1) / 2 : j / 2;
+    const double share = !red ? 0.0 : i == 2 ? 1.0 : 0.5;
+    // (three columns at a time hide each other's latency; all fifteen would take
+    // more registers than the rest of the kernel)
+#pragma unroll 3
+    for (int v = 0; v < 15; ++v) {
+        const double b = u == v ? 1.0 : 0.0;
+        double z = red ? b * inv : 0.0;
+        double s = nb(z);
+        z = red ? z : (b + s) * inv;
+        // the red residual, restricted to (2, 2J) along the diagonal
+        s = nb(z);
+        s = red ? s : 0.0;
+        const double c = s + 0.5 * (dpp<0x104>(s) + dpp<0x114>(s));
+        const double c0 = read_lane(c, 1), c1 = read_lane(c, 7), c2 = read_lane(c, 13);
+        const double y1 = c1 + e0 * r0 * c0;
+        const double x2 = (c2 + e1 * r1 * y1) * r2;
+        const double x1 = (y1 + e1 * x2) * r1, x0 = (c0 + e0 * x1) * r0;
+        z += share * (J == 0 ? x0 : J == 1 ? x1 : x2);
+        s = nb(z);
+        z = red ? z : (b + s) * inv;
+        s = nb(z);
+        if (t < 15) A[15 * v + u] = red ? (b + s) * inv : z;
+    }
+}
+
+// e2 = A (restriction of the level h = 1/8's red residuals), A from exact_build
+// or visit2_build; one wave
 template <bool FLOW, typename T>
 __device__ __forceinline__ void exact_solve(const T* rs3, const double* A, T* e2, int t = threadIdx.x)
 {

@@ -103,7 +103,7 @@ __device__ __forceinline__ void build_levels5(Levels5<T>& m, const T* k5, int t)
         coarse_weights(m.c3, m.c4.rs, t);
         coarsen<T, 2, 64>(m.c3.rs, t, cell(m.c4.rs, 8));
         wave_order();
-        exact_build<false>(m.c3.rs, m.cinv, t);
+        exact_build(m.c3.rs, m.cinv, t);
     }
 }
 template <typename T, int NT>
