@@ -85,12 +85,13 @@ int launch_loglik(mls2mc_ctx* ctx, int64_t N, const double* G, const double* y, 
 // Both take the midpoints and the comparisons of plain bisection.  Where the
 // line lies (us a call with its launches, inside / at an end; one workgroup
 // with plain bisection in global memory, launches, one workgroup with the
-// bracket): 2049 particles 150 / 13, 54 / 41-46, 52 / 13; 8192 283 / 18-22,
-// 67 / 43-46, 80 / 13; 16384 460 / 28-34, 76 / 45-50, about 150 / 19.  Beyond
-// 8192 an end costs up to 25 us more than in one workgroup (until about 30000),
-// a step inside 200 us and more less.
+// bracket): 2049 particles 150 / 13, 54 / 41-46, 52 / 13; 4096 196 / 13-16,
+// 60 / 43-46, 59 / 13; 8192 283 / 18-22, 67 / 43-46, 80 / 13; 16384 460 /
+// 28-34, 76 / 45-50, about 150 / 19.  Up to 4096 one workgroup loses neither;
+// beyond, the steps inside, most of a run's, decide for the launches, and an
+// end costs up to 30 us more than in one workgroup (until about 30000).
 constexpr int kNS = 1024;
-constexpr int64_t kStepSmall = 8192;
+constexpr int64_t kStepSmall = 4096;
 
 struct StepIn {
     int64_t N;
@@ -442,8 +443,7 @@ int launch_next_step(mls2mc_ctx* ctx, int64_t N, const double* d, double scale, 
         else if (N <= 512) next_step_small_kernel<512, 1><<<1, 512, 0, s>>>(A);
         else if (N <= 1024) next_step_small_kernel<512, 2><<<1, 512, 0, s>>>(A);
         else if (N <= 2048) next_step_small_kernel<1024, 2><<<1, 1024, 0, s>>>(A);
-        else if (N <= 4096) next_step_small_kernel<1024, 4><<<1, 1024, 0, s>>>(A);
-        else next_step_small_kernel<1024, 8><<<1, 1024, 0, s>>>(A);
+        else next_step_small_kernel<1024, 4><<<1, 1024, 0, s>>>(A);
         MLS_CHECK_HIP(hipGetLastError());
         return MLS2MC_OK;
     }

@@ -1,4 +1,4 @@
-"""The adaptive step between 2049 and 8192 particles, which brackets the root
+"""The adaptive step between 2049 and 4096 particles, which brackets the root
 before it bisects, against the oracle's plain bisection."""
 import numpy as np
 import pytest
